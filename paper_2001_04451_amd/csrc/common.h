@@ -122,6 +122,7 @@ __device__ __forceinline__ float dpp_f32(float x) {
 constexpr int kDppXor1 = 0xB1;        // quad_perm [1, 0, 3, 2]
 constexpr int kDppXor2 = 0x4E;        // quad_perm [2, 3, 0, 1]
 constexpr int kDppHalfMirror = 0x141; // lane 7 - i within each group of eight
+constexpr int kDppMirror = 0x140;     // lane 15 - i within each row of sixteen
 __device__ __forceinline__ float group8_sum(float x) {
     x += dpp_f32<kDppXor1>(x);
     x += dpp_f32<kDppXor2>(x);

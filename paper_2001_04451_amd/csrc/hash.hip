@@ -98,6 +98,7 @@ __global__ __launch_bounds__(64) void prep_r_cols_kernel(const float* __restrict
                                                          int* __restrict__ r_exp,
                                                          uint16_t* __restrict__ r_hi,
                                                          uint16_t* __restrict__ r_mid,
+                                                         float* __restrict__ r_t,
                                                          float* __restrict__ col_norm) {
     const int c = blockIdx.x, r = blockIdx.y, t = threadIdx.x;
     const int n_r = gridDim.y;
@@ -138,6 +139,7 @@ __global__ __launch_bounds__(64) void prep_r_cols_kernel(const float* __restrict
         n2 = sqrtf(s2);
     }
     const size_t o = ((size_t)r * half_pad + c) * kHeadDim + t;
+    r_t[o] = x;
     r_hi[o] = (uint16_t)hi;
     r_mid[o] = (uint16_t)mid;
     if (t == 0) {
@@ -178,30 +180,39 @@ __device__ __forceinline__ float q_value(const void* q, int64_t row, int k) {
     }
 }
 
-// Exact argmax of [xR; -xR] for the listed row-rounds of one round.  A
-// block takes the list in groups of 64 entries, one per lane of every wave,
-// in two passes:
-//  1. each wave forms the fp32 projections of its 32 columns for all 64
-//     entries (lane = entry): R's values are the same for every lane, so they
-//     are scalar loads (R[t][c0 .. c0+31] is contiguous), fetched one t ahead,
-//     and nothing is staged.  The fp32
-//     value is within eps = (64 * 2^-24 * 1.01 + 2^-46) * |q| * max_c |R_c|
-//     of the fp64 one, so only a column whose fp32 magnitude is within 2 eps
-//     of the entry's largest can hold the fp64 argmax;
+// Exact argmax of [xR; -xR] for the listed row-rounds of one round.  A block
+// keeps the round's R in registers and takes the list in groups of 16
+// entries, in two passes:
+//  1. fp32 projections of every column on the matrix cores
+//     (v_mfma_f32_16x16x4_f32: 16 columns x 16 entries).  Wave w owns columns
+//     64 w .. 64 w + 63 as four tiles; k-step s of lane group g is t = 16 g + s,
+//     so a lane holds 16 consecutive values of its entry's q row and, per
+//     tile, 16 consecutive values of its column (r_t: R with its columns
+//     contiguous), loaded once per block, all in flight together.  The fp32
+//     value is within
+//       eps = (64 * 2^-23 + 64 * 2^-24) * 1.05 * |q| * max_c |R_c|
+//     of the exact one (64 additions to within an ulp, products to within
+//     half), in any order, so only a column whose fp32 magnitude is within
+//     2 eps of the entry's largest can hold the exact argmax;
 //  2. for those candidates, the projection as the oracle forms it: the
 //     left-to-right sum over t of the exact products q_t * R_tc in fp64, one
-//     lane per (entry, candidate), sixteen candidate lanes per entry.  Ties go
+//     lane per (entry, candidate), eight candidate lanes per entry.  Ties go
 //     to the first index of [xR; -xR].
-// An entry with more than sixteen candidates (q = 0 makes every column one),
-// or none (a non-finite q), takes the plain fp64 pass over every column,
-// one wave per entry.
-constexpr int kRefineThreads = 1024;
+// An entry with more than eight candidates, or whose |q| max_c |R_c| leaves
+// the range in which eps bounds fp32's error (q = 0 and non-finite rows among
+// them), takes the plain fp64 pass over every column, one wave per entry.
+// Bound by latency: launch, a chain of dependent loads (count, list, q; R
+// beside them; the candidates' columns) and the instruction fetch of code
+// that each block runs once, so loops stay rolled where that costs little.
+// Measured against the earlier form (lane = entry, R by scalar loads one t
+// after another, 64 entries a block): 32 -> 6.2 us at L = 1K fp32, 23 -> 9.4
+// at 4 x 8 x 4K with 64 buckets, 39 -> 29 at 16 x 64K with 8 rounds of 1024.
+constexpr int kRefineThreads = 512;
 constexpr int kRefineWaves = kRefineThreads / 64;
-constexpr int kRefineGroup = 64;     // entries per pass
-constexpr int kRefineCand = 16;      // candidate lanes per entry
-constexpr int kRefineCols = 32;      // columns per wave in pass 1
-static_assert(kRefineWaves * kRefineCols >= 512, "pass 1 covers n_b / 2 <= 512 columns");
-static_assert(kRefineWaves * 64 == kRefineGroup * kRefineCand, "pass 2 lanes");
+constexpr int kRefineGroup = 16;     // entries per pass: a matrix tile's columns
+constexpr int kRefineCand = 8;       // candidate lanes per entry
+constexpr int kRefineTiles = 4;      // 16-column tiles per wave in pass 1
+static_assert(kRefineWaves * kRefineTiles * 16 >= 512, "pass 1 covers n_b / 2 <= 512 columns");
 
 __device__ __forceinline__ void better(double v, int i, double& bv, int& bi) {
     if (v > bv || (v == bv && i < bi)) {
@@ -211,7 +222,7 @@ __device__ __forceinline__ void better(double v, int i, double& bv, int& bi) {
 }
 
 struct RefineShared {
-    float qs[kRefineGroup][kHeadDim + 1];  // the group's q rows
+    float qs[kRefineGroup][kHeadDim + 4];  // the group's q rows
     float qn[kRefineGroup];                // and their norms
     float mx[kRefineWaves][kRefineGroup];  // per wave: largest |fp32 projection| of each entry
     int cnt[kRefineGroup];                 // candidates found per entry
@@ -219,138 +230,146 @@ struct RefineShared {
 };
 
 template <bool F32>
-__global__ __launch_bounds__(kRefineThreads, 1) void hash_refine_kernel(const void* __restrict__ q,
-                                                          const float* __restrict__ R, int half,
-                                                          int n_r, int64_t list_stride,
-                                                          const int* __restrict__ lists,
-                                                          const int* __restrict__ counts,
-                                                          const float* __restrict__ col_norm_max,
-                                                          const int* __restrict__ r_exp,
-                                                          int32_t* __restrict__ buckets) {
-    __shared__ RefineShared S;
+__global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
+    const void* __restrict__ q, const float* __restrict__ r_t, int half, int half_pad, int n_r, int64_t list_stride,
+    const int* __restrict__ lists, const int* __restrict__ counts, const float* __restrict__ col_norm_max,
+    const int* __restrict__ r_exp, int32_t* __restrict__ buckets) {
+    __shared__ __attribute__((aligned(16))) RefineShared S;
     const int r = blockIdx.y;
     const int n = counts[r];
     const int groups = (n + kRefineGroup - 1) / kRefineGroup;
     if ((int)blockIdx.x >= groups) return;  // uniform per block
     const int* list = lists + list_stride * r;
-    const float* Rr = R + (size_t)r * kHeadDim * half;  // [t][half]
-    const int lane = lane_id();
+    const float* Rt = r_t + (size_t)r * half_pad * kHeadDim;  // [column][t], zero columns up to half_pad
+    const int lane = lane_id(), e16 = lane & 15, g16 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // max_c |R_c| of the round as given (the planes' norms are of R * 2^r_exp)
     const float cn = r_exp ? ldexpf(col_norm_max[r], -r_exp[r]) : col_norm_max[r];
-    const int c0 = wave * kRefineCols;  // this wave's columns in pass 1
-    const int ncols = max(0, min(kRefineCols, half - c0));
+    const int c0 = wave * kRefineTiles * 16;  // this wave's columns in pass 1
+    const bool has_cols = c0 < half;          // uniform per wave
+    f32x4 rc[kRefineTiles][4];                // column c0 + 16 tile + e16 (clamped), t = 16 g16 ..
+    if (has_cols) {
+#pragma unroll
+        for (int tile = 0; tile < kRefineTiles; ++tile) {
+            const f32x4* src = reinterpret_cast<const f32x4*>(
+                Rt + (size_t)min(c0 + 16 * tile + e16, half - 1) * kHeadDim + 16 * g16);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) rc[tile][k] = src[k];
+        }
+    }
 
     for (int g = blockIdx.x; g < groups; g += gridDim.x) {
-        if (wave == 0) {
-            // the group's q rows, one per lane, into LDS
-            const int64_t row = list[min(g * kRefineGroup + lane, n - 1)];
-            float qr[kHeadDim];
+        if (threadIdx.x < kRefineGroup) S.cnt[threadIdx.x] = 0;
+        // pass 1: the waves with columns (wave 0 always has some, and also
+        // keeps the q rows for pass 2)
+        f32x4 p[kRefineTiles] = {};
+        if (has_cols) {
+            const int64_t row = list[min(g * kRefineGroup + e16, n - 1)];
+            f32x4 qv[4];
             if constexpr (F32) {
-                const f32x4* src = reinterpret_cast<const f32x4*>(static_cast<const float*>(q) + row * kHeadDim);
+                const f32x4* src = reinterpret_cast<const f32x4*>(static_cast<const float*>(q) + row * kHeadDim + 16 * g16);
 #pragma unroll
-                for (int t4 = 0; t4 < kHeadDim / 4; ++t4) {
-                    const f32x4 x = src[t4];
-#pragma unroll
-                    for (int e2 = 0; e2 < 4; ++e2) qr[4 * t4 + e2] = x[e2];
-                }
+                for (int k = 0; k < 4; ++k) qv[k] = src[k];
             } else {
-                const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(q) + row * kHeadDim);
+                const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(q) + row * kHeadDim + 16 * g16);
 #pragma unroll
-                for (int t8 = 0; t8 < kHeadDim / 8; ++t8) {
-                    const u32x4 x = src[t8];
+                for (int k = 0; k < 2; ++k) {
+                    const u32x4 x = src[k];
 #pragma unroll
-                    for (int e2 = 0; e2 < 4; ++e2) {
-                        qr[8 * t8 + 2 * e2] = __uint_as_float(x[e2] << 16);
-                        qr[8 * t8 + 2 * e2 + 1] = __uint_as_float(x[e2] & 0xFFFF0000u);
+                    for (int e = 0; e < 4; ++e) {
+                        qv[2 * k + e / 2][2 * (e & 1)] = __uint_as_float(x[e] << 16);
+                        qv[2 * k + e / 2][2 * (e & 1) + 1] = __uint_as_float(x[e] & 0xFFFF0000u);
                     }
                 }
             }
-            float ss = 0.f;
+            if (wave == 0) {
+                float ss = 0.f;
 #pragma unroll
-            for (int t = 0; t < kHeadDim; ++t) {
-                ss = fmaf(qr[t], qr[t], ss);
-                S.qs[lane][t] = qr[t];
+                for (int k = 0; k < 4; ++k) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ss = fmaf(qv[k][e], qv[k][e], ss);
+                    *reinterpret_cast<f32x4*>(&S.qs[e16][16 * g16 + 4 * k]) = qv[k];
+                }
+                ss = sum_xor32(sum_xor16(ss));
+                if (g16 == 0) S.qn[e16] = sqrtf(ss);
             }
-            S.qn[lane] = sqrtf(ss);
-            S.cnt[lane] = 0;
+            // p[tile][j]: |projection| of column c0 + 16 tile + 4 g16 + j for entry e16
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+#pragma unroll
+                for (int tile = 0; tile < kRefineTiles; ++tile)
+                    p[tile] = __builtin_amdgcn_mfma_f32_16x16x4f32(rc[tile][s >> 2][s & 3], qv[s >> 2][s & 3], p[tile],
+                                                                   0, 0, 0);
+            float m = 0.f;
+#pragma unroll
+            for (int tile = 0; tile < kRefineTiles; ++tile)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float a = fabsf(p[tile][j]);
+                    // a column past the round: below any cut
+                    p[tile][j] = c0 + 16 * tile + 4 * g16 + j < half ? a : -1.f;
+                    m = fmaxf(m, p[tile][j]);
+                }
+            m = max_xor32(max_xor16(m));
+            if (g16 == 0) S.mx[wave][e16] = m;
+        } else if (lane < kRefineGroup) {
+            S.mx[wave][lane] = 0.f;
+        }
+        __syncthreads();
+        if (has_cols) {
+            float mx = S.mx[0][e16];
+#pragma unroll
+            for (int w = 1; w < kRefineWaves; ++w) mx = fmaxf(mx, S.mx[w][e16]);
+            // |q| max |R_c| bounds every partial sum: above fp32's range a sum
+            // may overflow, and far below it products lose bits that eps does
+            // not count; such an entry gets no candidates
+            const float size = S.qn[e16] * cn;
+            const float eps = (float)(64 * (0x1p-23 + 0x1p-24) * 1.05) * size;
+            const float cut = size > 0x1p-80f && size < 0x1p120f ? fmaxf(mx - 2.f * eps, 0.f) : __builtin_inff();
+            uint32_t mine = 0;  // bit 4 tile + j: a candidate
+#pragma unroll
+            for (int tile = 0; tile < kRefineTiles; ++tile)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) mine |= (uint32_t)(p[tile][j] >= cut) << (4 * tile + j);
+            while (mine) {
+                const int jj = __ffs((int)mine) - 1;
+                mine &= mine - 1;
+                const int k = atomicAdd(&S.cnt[e16], 1);
+                if (k < kRefineCand) S.cand[e16][k] = c0 + 16 * (jj >> 2) + 4 * g16 + (jj & 3);
+            }
         }
         __syncthreads();
 
-        // pass 1: fp32 projections of columns c0 .. c0+ncols-1 for the
-        // lane's entry; the next t's R values and q value are loaded before
-        // the current t's products
-        float p[kRefineCols];
-#pragma unroll
-        for (int j = 0; j < kRefineCols; ++j) p[j] = 0.f;
-        auto pass1 = [&](auto full_tag) {
-            constexpr bool FULL = decltype(full_tag)::value;  // ncols == kRefineCols
-            const int last = ncols - 1;
-            auto col = [&](int j) { return FULL ? j : min(j, last); };
-            float rc[kRefineCols], qt = S.qs[lane][0];
-#pragma unroll
-            for (int j = 0; j < kRefineCols; ++j) rc[j] = Rr[c0 + col(j)];
-            for (int t = 0; t < kHeadDim; ++t) {
-                const int tn = min(t + 1, kHeadDim - 1);
-                float rn[kRefineCols];
-                const float* rt = Rr + (size_t)tn * half + c0;
-#pragma unroll
-                for (int j = 0; j < kRefineCols; ++j) rn[j] = rt[col(j)];
-                const float qn = S.qs[lane][tn];
-#pragma unroll
-                for (int j = 0; j < kRefineCols; ++j) p[j] = fmaf(qt, rc[j], p[j]);
-#pragma unroll
-                for (int j = 0; j < kRefineCols; ++j) rc[j] = rn[j];
-                qt = qn;
-            }
-        };
-        if (ncols == kRefineCols)
-            pass1(std::true_type{});
-        else if (ncols > 0)
-            pass1(std::false_type{});
-        float mxl = 0.f;
-#pragma unroll
-        for (int j = 0; j < kRefineCols; ++j)
-            if (j < ncols) mxl = fmaxf(mxl, fabsf(p[j]));
-        S.mx[wave][lane] = mxl;
-        __syncthreads();
-        float mx = 0.f;
-#pragma unroll
-        for (int w = 0; w < kRefineWaves; ++w) mx = fmaxf(mx, S.mx[w][lane]);
-        const float eps = (float)((64.0 * 0x1p-24 * 1.01 + 0x1p-46) * 1.01) * S.qn[lane] * cn;
-        const float cut = mx - 2.f * eps;
-#pragma unroll
-        for (int j = 0; j < kRefineCols; ++j)
-            if (j < ncols && fabsf(p[j]) >= cut) {
-                const int k = atomicAdd(&S.cnt[lane], 1);
-                if (k < kRefineCand) S.cand[lane][k] = c0 + j;
-            }
-        __syncthreads();
-
-        // pass 2: lane = (entry i, candidate k), four entries per wave
-        {
-            const int i = wave * (kRefineGroup / kRefineWaves) + lane / kRefineCand;
+        // pass 2: lane = (entry i, candidate k), eight entries per wave
+        if (wave < kRefineGroup * kRefineCand / 64) {
+            const int i = wave * (64 / kRefineCand) + lane / kRefineCand;
             const int k = lane % kRefineCand;
             const int ci = S.cnt[i];
             double bv = -__builtin_inf();
             int bi = 0x7FFFFFFF;
-            if (ci >= 1 && ci <= kRefineCand && k < ci) {
-                const int c = S.cand[i][k];
+            const int ei = g * kRefineGroup + i;
+            const int row = list[min(ei, n - 1)];  // loaded beside the columns
+            if (k < ci && ci <= kRefineCand) {
+                const int cc = S.cand[i][k];
+                const f32x4* col = reinterpret_cast<const f32x4*>(Rt + (size_t)cc * kHeadDim);
                 // q_t * R_tc is exact in fp64 (at most 48 significant bits), so
                 // whether the compiler fuses the multiply into the add or not,
                 // the sum rounds exactly as the plain loop does.
-                // R's column in runs of 16 values, all of a run's loads in flight together
                 double acc = 0.0;
-                for (int t0 = 0; t0 < kHeadDim; t0 += 16) {
-                    float rcol[16];
+#pragma unroll 1
+                for (int u0 = 0; u0 < 16; u0 += 8) {
+                    f32x4 xr[8];
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) rcol[u] = Rr[(size_t)(t0 + u) * half + c];
+                    for (int u = 0; u < 8; ++u) xr[u] = col[u0 + u];
 #pragma unroll
-                    for (int u = 0; u < 16; ++u)
-                        acc = __dadd_rn(acc, __dmul_rn((double)S.qs[i][t0 + u], (double)rcol[u]));
+                    for (int u = 0; u < 8; ++u) {
+                        const f32x4 xq = *reinterpret_cast<const f32x4*>(&S.qs[i][4 * (u0 + u)]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc = __dadd_rn(acc, __dmul_rn((double)xq[e], (double)xr[u][e]));
+                    }
                 }
-                better(acc, c, bv, bi);
-                better(-acc, half + c, bv, bi);
+                better(acc, cc, bv, bi);
+                better(-acc, half + cc, bv, bi);
             }
 #pragma unroll
             for (int o = 1; o < kRefineCand; o <<= 1) {
@@ -358,24 +377,30 @@ __global__ __launch_bounds__(kRefineThreads, 1) void hash_refine_kernel(const vo
                 const int oi = __shfl_xor(bi, o);
                 better(ov, oi, bv, bi);
             }
-            const int ei = g * kRefineGroup + i;
-            if (k == 0 && ei < n && ci >= 1 && ci <= kRefineCand) buckets[(int64_t)list[ei] * n_r + r] = bi;
+            if (k == 0 && ei < n && ci >= 1 && ci <= kRefineCand) buckets[(int64_t)row * n_r + r] = bi;
         }
 
-        // entries with too many candidates: every column in fp64, one wave each
+        // entries left to fp64: every column, one wave each
         for (int i = wave; i < kRefineGroup; i += kRefineWaves) {
             const int ei = g * kRefineGroup + i;
             const int ci = S.cnt[i];
             if (ei >= n || (ci >= 1 && ci <= kRefineCand)) continue;  // uniform per wave
             double bv = -__builtin_inf();
             int bi = 0x7FFFFFFF;
+#pragma unroll 1
             for (int c = lane; c < half; c += 64) {
                 double acc = 0.0;
-                for (int t = 0; t < kHeadDim; ++t)
-                    acc = __dadd_rn(acc, __dmul_rn((double)S.qs[i][t], (double)Rr[(size_t)t * half + c]));
+#pragma unroll 4
+                for (int u = 0; u < 16; ++u) {
+                    const f32x4 xq = *reinterpret_cast<const f32x4*>(&S.qs[i][4 * u]);
+                    const f32x4 xr = reinterpret_cast<const f32x4*>(Rt + (size_t)c * kHeadDim)[u];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc = __dadd_rn(acc, __dmul_rn((double)xq[e], (double)xr[e]));
+                }
                 better(acc, c, bv, bi);
                 better(-acc, half + c, bv, bi);
             }
+#pragma unroll 1
             for (int o = 32; o >= 1; o >>= 1) {
                 const double ov = __shfl_xor(bv, o);
                 const int oi = __shfl_xor(bi, o);
@@ -1031,6 +1056,7 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
 struct HashWs {
     uint16_t* r_hi;
     uint16_t* r_mid;
+    float* r_t;       // R as given, [n_r][half_pad][64] (columns contiguous, zero padded)
     float* col_norm;  // [3][n_r][half_pad]: |R_c|, |R_c - hi_c|, |R_c - hi_c - mid_c|
     float* norm_max;  // [3][n_r]: the largest of each
     int* r_exp;       // [n_r]: binary16 planes hold R * 2^r_exp (bf16 input)
@@ -1056,6 +1082,8 @@ HashWs carve(void* base, int64_t rows, int n_rounds, int half_pad) {
     off += align256(per * 2);
     w.r_mid = reinterpret_cast<uint16_t*>(p + off);
     off += align256(per * 2);
+    w.r_t = reinterpret_cast<float*>(p + off);
+    off += align256(per * 4);
     w.col_norm = reinterpret_cast<float*>(p + off);
     off += align256((size_t)3 * n_rounds * half_pad * 4);
     w.norm_max = reinterpret_cast<float*>(p + off);
@@ -1144,11 +1172,11 @@ hipError_t launch_hash(const void* q, bool f32, int64_t rows, int n_rounds, int 
 
     if (f32) {
         prep_r_cols_kernel<false><<<dim3(half_pad, n_rounds), 64, 0, stream>>>(
-            R, half, half_pad, nullptr, nullptr, w.r_hi, w.r_mid, w.col_norm);
+            R, half, half_pad, nullptr, nullptr, w.r_hi, w.r_mid, w.r_t, w.col_norm);
     } else {
         prep_r_part_kernel<<<dim3(kScaleParts, n_rounds), 256, 0, stream>>>(R, half, w.r_part);
         prep_r_cols_kernel<true><<<dim3(half_pad, n_rounds), 64, 0, stream>>>(
-            R, half, half_pad, w.r_part, w.r_exp, w.r_hi, w.r_mid, w.col_norm);
+            R, half, half_pad, w.r_part, w.r_exp, w.r_hi, w.r_mid, w.r_t, w.col_norm);
     }
     prep_r_max_kernel<<<dim3(n_rounds, 3), 256, 0, stream>>>(w.col_norm, n_rounds, half_pad, w.norm_max,
                                                              w.count, n_rounds * (kSegs + 1));
@@ -1172,17 +1200,18 @@ hipError_t launch_hash(const void* q, bool f32, int64_t rows, int n_rounds, int 
 
     constexpr int kWaves = kHashWaves;
     const unsigned grid = (unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock);
-    // Refinement blocks per round: a typical list holds well under 1% of the
-    // rows, a few groups of 64 per round; longer lists are strided.
-    const unsigned refine_blocks =
-        (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (rows + kRefineGroup - 1) / kRefineGroup));
+    // Refinement blocks: about two per CU over all rounds.  A typical list holds
+    // 0.1% of the rows (64 groups of 16 at 1M rows); longer lists are strided,
+    // and a block keeps its R for all of its groups.
+    const unsigned refine_blocks = (unsigned)std::max<int64_t>(
+        1, std::min<int64_t>(std::max(1, 512 / n_rounds), (rows + kRefineGroup - 1) / kRefineGroup));
     if (f32) {
         launch_pass<true, kExact, kWaves>(
             PassArgs{q, rows, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, nullptr, acc_f32, nullptr, 0.f,
                      err_pack, nullptr, buckets, nullptr, nullptr, w.list2, count2, 0},
             dim3(grid), n_rounds, stream);
         hash_refine_kernel<true><<<dim3(refine_blocks, n_rounds), kRefineThreads, 0, stream>>>(
-            q, R, half, n_rounds, rows, w.list2, count2, cn_max, nullptr, buckets);
+            q, w.r_t, half, half_pad, n_rounds, rows, w.list2, count2, cn_max, nullptr, buckets);
     } else {
         // screen with R's hi plane; the rows it leaves open get both planes;
         // what those leave open gets the fp64 refinement
@@ -1203,7 +1232,7 @@ hipError_t launch_hash(const void* q, bool f32, int64_t rows, int n_rounds, int 
                      err_pack, nullptr, buckets, w.list1, count1, w.list2, count2, w.seg_cap},
             dim3(per_round, 1, n_rounds), 1, stream);
         hash_refine_kernel<false><<<dim3(refine_blocks, n_rounds), kRefineThreads, 0, stream>>>(
-            q, R, half, n_rounds, rows, w.list2, count2, cn_max, w.r_exp, buckets);
+            q, w.r_t, half, half_pad, n_rounds, rows, w.list2, count2, cn_max, w.r_exp, buckets);
     }
     return hipGetLastError();
 }

@@ -1,0 +1,48 @@
+"""The hash's last pass (fp64) at the edges of its groups, candidate lists and
+fp32 range.  Bucket ids are whole numbers: bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import log, small, to_device
+from paper_2001_04451_amd import lsh
+from paper_2001_04451_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    lsh.lib()
+
+
+# copies: columns within an ulp of one another, so that every row has that
+# many candidates: two, all of a row's eight candidate lanes, and more (every
+# column in fp64).  Lengths: one row, groups of 16 with a remainder, several
+# groups.  scale 2^-120 on top of R's 2^-30 leaves fp32's range.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("L,n_buckets,copies,k", [(1, 2, 1, 0), (17, 32, 2, 0), (33, 128, 8, 0), (65, 128, 9, 0),
+                                                  (300, 1022, 3, 0), (40, 66, 2, -120)])
+def test_hash_close_columns(gpu, dtype, L, n_buckets, copies, k):
+    w = small("causal_bf16_L16384", B=1, H=2, L=L, n_buckets=n_buckets, n_rounds=2, dtype=dtype)
+    x = W.make_inputs(w)
+    R = x["R"].copy()
+    half = n_buckets // 2
+    for c in range(half):  # runs of `copies` columns, each one ulp away in one entry
+        base = c - c % copies
+        R[:, :, c] = R[:, :, base]
+        if c != base:
+            R[:, c % 64, c] = np.nextafter(R[:, c % 64, c], np.float32(np.inf))
+    q = W.as_f64(x["q"], dtype).astype(np.float32)
+    if k:
+        q = np.ldexp(q, k).astype(np.float32)
+        R = np.ldexp(R, -30).astype(np.float32)
+    qin = W.f32_to_bf16_bits(q) if dtype == "bf16" else q
+    want, _ = oracle.lsh_hash(W.as_f64(qin, dtype), R.astype(np.float64))
+    log("hash-close", dtype, L, n_buckets, copies, k)
+    got = lsh.lsh_hash(lsh.Config.of(w), to_device(qin, dtype), to_device(R, "f32")).cpu().numpy()
+    assert np.array_equal(got, want)
