@@ -39,38 +39,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kRB = 2;  // 32-row blocks per wave: each staged R tile feeds 2 * 8 MFMAs
 
-// Largest |R| of each 1/kScaleParts of each round (block (part, r)): the
-// fp16 planes' scale is taken from these partial maxima.
-constexpr int kScaleParts = 32;
-
-__global__ __launch_bounds__(256) void prep_r_part_kernel(const float* __restrict__ R, int half,
-                                                          float* __restrict__ r_part) {
-    __shared__ float red[4];
-    const int part = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
-    const int n = kHeadDim * half;
-    const int per = (n + kScaleParts - 1) / kScaleParts;
-    const int lo = part * per, hi = min(n, lo + per);
-    const float* Rr = R + (size_t)r * n;
-    float m = 0.f;
-    for (int i = lo + tid; i < hi; i += 256) m = fmaxf(m, fabsf(Rr[i]));
-    m = wave_max(m);
-    if ((tid & 63) == 0) red[tid >> 6] = m;
-    __syncthreads();
-    if (tid == 0) r_part[r * kScaleParts + part] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-
-// The exponent sr with max |R| * 2^sr in [2^14, 2^15) (0 when the round is
-// zero or not finite): a positive scale of a whole round leaves every
-// argmax unchanged.
-__device__ __forceinline__ int round_scale_exp(const float* __restrict__ part) {
-    float m = 0.f;
-    for (int i = 0; i < kScaleParts; ++i) m = fmaxf(m, part[i]);
-    // m in [2^e, 2^(e+1)) (frexp: m = f 2^k with f in [0.5, 1), e = k - 1)
-    int k = 0;
-    (void)frexpf(m, &k);
-    return (m > 0.f && m <= 3.4e38f) ? 14 - (k - 1) : 0;
-}
-
 // x * 2^e for |e| up to 254, in two exact steps.
 __device__ __forceinline__ double ldexp2(double x, int e) {
     const int a = e / 2;
@@ -85,90 +53,128 @@ __device__ __forceinline__ uint32_t f16_normal_bits(double x) {
     return (uint32_t)__builtin_bit_cast(uint16_t, h);
 }
 
-// One R column per block of 64 lanes (lane = t): two 16-bit planes hi/mid,
-// [n_r][half_pad][64] (column contiguous, zero padded), and three 2-norms of
-// the column, [3][n_r][half_pad]: |R_c|, |R_c - hi_c|, |R_c - hi_c - mid_c|.
-//  * F16 (bf16 input): binary16 planes of R_c * 2^sr[r] (sr from the
-//    round's partial maxima, also written to r_exp); the norms are of the
-//    scaled column, formed in fp64 from exact residuals.
+// R's planes and norms: two 16-bit planes hi/mid and R itself,
+// [round][half_pad][64] (column contiguous, zero padded); three 2-norms of
+// every column, [3][rounds][half_pad]: |R_c|, |R_c - hi_c|,
+// |R_c - hi_c - mid_c|, and the largest of each, [3][rounds].
+//  * F16 (bf16 input): binary16 planes of R_c * 2^sr, sr (in r_exp) bringing
+//    the round's largest |R| into [2^14, 2^15), 0 when the round is zero or
+//    not finite (a positive scale of a whole round leaves every argmax
+//    unchanged); the norms are of the scaled column.
 //  * bf16 planes (fp32 input): R = hi + mid + res with each step exact.
+// The norms are formed in fp64 from exact residuals.  A block takes 64
+// columns of a round, wave w the t's 4 w .. 4 w + 3 of them, and for F16
+// looks the whole round (at most 128 KB, in the L2 after the first block)
+// over for its largest |R| by itself, so that the scale needs no launch of
+// its own.  A round of one block also needs none for the norms' maxima (up to
+// 128 buckets: one launch instead of three, 12 -> 5 us); longer ones take
+// prep_r_max_kernel.  The first block of a round clears its list counters.
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepCols = 64;
+
 template <bool F16>
-__global__ __launch_bounds__(64) void prep_r_cols_kernel(const float* __restrict__ R, int half,
-                                                         int half_pad, const float* __restrict__ r_part,
-                                                         int* __restrict__ r_exp,
-                                                         uint16_t* __restrict__ r_hi,
-                                                         uint16_t* __restrict__ r_mid,
-                                                         float* __restrict__ r_t,
-                                                         float* __restrict__ col_norm) {
-    const int c = blockIdx.x, r = blockIdx.y, t = threadIdx.x;
-    const int n_r = gridDim.y;
-    const float x = c < half ? R[((size_t)r * kHeadDim + t) * half + c] : 0.f;
-    uint32_t hi, mid;
-    float n0, n1, n2;
-    if constexpr (F16) {
-        const int sr = round_scale_exp(r_part + r * kScaleParts);
-        if (c == 0 && t == 0) r_exp[r] = sr;
-        const double xs = ldexp2((double)x, sr);
-        hi = f16_normal_bits(xs);
-        const double res = xs - (double)f16_bits_to_f32(hi);  // exact in fp64
-        mid = f16_normal_bits(res);
-        const double res2 = res - (double)f16_bits_to_f32(mid);  // exact
-        double s0 = xs * xs, s1 = res * res, s2 = res2 * res2;
-        for (int off = 32; off >= 1; off >>= 1) {
-            s0 += __shfl_xor(s0, off);
-            s1 += __shfl_xor(s1, off);
-            s2 += __shfl_xor(s2, off);
-        }
-        // rounded up to fp32 (the bounds that use them are upper bounds)
-        n0 = (float)sqrt(s0) * (1.f + 0x1p-22f);
-        n1 = (float)sqrt(s1) * (1.f + 0x1p-22f);
-        n2 = (float)sqrt(s2) * (1.f + 0x1p-22f);
-    } else {
-        hi = f32_to_bf16_bits(x);
-        const float res = x - bf16_bits_to_f32(hi);  // exact (Sterbenz)
-        mid = f32_to_bf16_bits(res);
-        const float res2 = res - bf16_bits_to_f32(mid);  // exact
-        float s0 = x * x, s1 = res * res, s2 = res2 * res2;
-        for (int off = 32; off >= 1; off >>= 1) {
-            s0 += __shfl_xor(s0, off);
-            s1 += __shfl_xor(s1, off);
-            s2 += __shfl_xor(s2, off);
-        }
-        n0 = sqrtf(s0);
-        n1 = sqrtf(s1);
-        n2 = sqrtf(s2);
+__global__ __launch_bounds__(kPrepThreads) void prep_r_kernel(
+    const float* __restrict__ R, int half, int half_pad, int* __restrict__ r_exp, uint16_t* __restrict__ r_hi,
+    uint16_t* __restrict__ r_mid, float* __restrict__ r_t, float* __restrict__ col_norm, float* __restrict__ norm_max,
+    int* __restrict__ seg_counts, int n_segs, int* __restrict__ counts) {
+    constexpr int T = kHeadDim * kPrepCols / kPrepThreads;  // t's per thread
+    static_assert(T == 4 && kPrepCols == 64, "a wave per four t's");
+    constexpr int kWaves = kPrepThreads / 64;
+    __shared__ double sums[3][kPrepThreads];
+    __shared__ float red[kWaves];
+    const int r = blockIdx.y, n_r = gridDim.y, tid = threadIdx.x, lane = tid & 63;
+    const int sp = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blockIdx.x == 0) {
+        if (tid < n_segs) seg_counts[(size_t)r * n_segs + tid] = 0;
+        if (tid == 0) counts[r] = 0;
     }
-    const size_t o = ((size_t)r * half_pad + c) * kHeadDim + t;
-    r_t[o] = x;
-    r_hi[o] = (uint16_t)hi;
-    r_mid[o] = (uint16_t)mid;
-    if (t == 0) {
-        const size_t plane = (size_t)n_r * half_pad, k = (size_t)r * half_pad + c;
-        col_norm[k] = n0;
-        col_norm[plane + k] = n1;
-        col_norm[2 * plane + k] = n2;
+    const int c = blockIdx.x * kPrepCols + lane;
+    const bool live = c < half_pad;
+    const float* Rr = R + (size_t)r * kHeadDim * half;
+    float x[T];
+#pragma unroll
+    for (int j = 0; j < T; ++j) x[j] = Rr[(size_t)(sp * T + j) * half + min(c, half - 1)];
+    int sr = 0;
+    if constexpr (F16) {
+        const int n = kHeadDim * half;
+        float m = 0.f;
+#pragma unroll 8
+        for (int i = tid; i < n; i += kPrepThreads) m = fmaxf(m, fabsf(Rr[i]));
+        m = wave_max(m);
+        if (lane == 0) red[sp] = m;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) m = fmaxf(m, red[i]);
+        // m in [2^e, 2^(e+1)) (frexp: m = f 2^k with f in [0.5, 1), e = k - 1)
+        int k = 0;
+        (void)frexpf(m, &k);
+        sr = (m > 0.f && m <= 3.4e38f) ? 14 - (k - 1) : 0;
+        if (blockIdx.x == 0 && tid == 0) r_exp[r] = sr;
+    }
+    double s0 = 0., s1 = 0., s2 = 0.;
+    uint32_t hi[T / 2], mid[T / 2];
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+        if (c >= half) x[j] = 0.f;
+        const double xs = F16 ? ldexp2((double)x[j], sr) : (double)x[j];
+        uint32_t hb, mb;
+        double res, res2;
+        if constexpr (F16) {
+            hb = f16_normal_bits(xs);
+            res = xs - (double)f16_bits_to_f32(hb);  // exact in fp64
+            mb = f16_normal_bits(res);
+            res2 = res - (double)f16_bits_to_f32(mb);  // exact
+        } else {
+            hb = f32_to_bf16_bits(x[j]);
+            const float rs = x[j] - bf16_bits_to_f32(hb);  // exact (Sterbenz)
+            mb = f32_to_bf16_bits(rs);
+            res = (double)rs;
+            res2 = (double)(rs - bf16_bits_to_f32(mb));  // exact
+        }
+        s0 += xs * xs;
+        s1 += res * res;
+        s2 += res2 * res2;
+        hi[j / 2] = j & 1 ? hi[j / 2] | (hb << 16) : hb;
+        mid[j / 2] = j & 1 ? mid[j / 2] | (mb << 16) : mb;
+    }
+    if (live) {
+        const size_t o = ((size_t)r * half_pad + c) * kHeadDim + sp * T;
+        *reinterpret_cast<f32x4*>(r_t + o) = f32x4{x[0], x[1], x[2], x[3]};
+        *reinterpret_cast<uint2*>(r_hi + o) = make_uint2(hi[0], hi[1]);
+        *reinterpret_cast<uint2*>(r_mid + o) = make_uint2(mid[0], mid[1]);
+    }
+    sums[0][tid] = s0;
+    sums[1][tid] = s1;
+    sums[2][tid] = s2;
+    __syncthreads();
+    if (sp < 3) {  // wave w: norm w of the block's columns
+        double t = 0.;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) t += sums[sp][64 * k + lane];
+        // rounded up to fp32 (the bounds that use them are upper bounds)
+        const float n = live ? (float)sqrt(t) * (1.f + 0x1p-22f) : 0.f;
+        if (live) col_norm[((size_t)sp * n_r + r) * half_pad + c] = n;
+        if (gridDim.x == 1) {
+            const float mw = wave_max(n);
+            if (lane == 0) norm_max[(size_t)sp * n_r + r] = mw;
+        }
     }
 }
 
-// Largest of each column norm per round (block (r, which)); block (0, 0)
-// also clears the n_clear list counters.
-__global__ __launch_bounds__(256) void prep_r_max_kernel(const float* __restrict__ col_norm, int n_r,
-                                                         int half_pad, float* __restrict__ norm_max,
-                                                         int* __restrict__ counts, int n_clear) {
-    __shared__ float red[256];
-    const int r = blockIdx.x, which = blockIdx.y;
-    if (r == 0 && which == 0)
-        for (int i = threadIdx.x; i < n_clear; i += blockDim.x) counts[i] = 0;
+// Largest of each column norm per round (block (round, which)), for rounds
+// of more than one prep block.
+__global__ __launch_bounds__(512) void prep_r_max_kernel(const float* __restrict__ col_norm, int n_r, int half_pad,
+                                                         float* __restrict__ norm_max) {
+    __shared__ float red[8];
+    const int r = blockIdx.x, which = blockIdx.y, tid = threadIdx.x;
     const float* cn = col_norm + ((size_t)which * n_r + r) * half_pad;
-    float mx = 0.f;
-    for (int c = threadIdx.x; c < half_pad; c += blockDim.x) mx = fmaxf(mx, cn[c]);
-    red[threadIdx.x] = mx;
+    float mx = wave_max(tid < half_pad ? cn[tid] : 0.f);  // half_pad <= 512
+    if ((tid & 63) == 0) red[tid >> 6] = mx;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
-        __syncthreads();
+    if (tid < 8) {
+        mx = group8_max(red[tid]);
+        if (tid == 0) norm_max[which * n_r + r] = mx;
     }
-    if (threadIdx.x == 0) norm_max[which * n_r + r] = red[0];
 }
 
 template <bool F32>
@@ -233,12 +239,13 @@ template <bool F32>
 __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
     const void* __restrict__ q, const float* __restrict__ r_t, int half, int half_pad, int n_r, int64_t list_stride,
     const int* __restrict__ lists, const int* __restrict__ counts, const float* __restrict__ col_norm_max,
-    const int* __restrict__ r_exp, int32_t* __restrict__ buckets) {
+    const int* __restrict__ r_exp, int32_t* __restrict__ buckets_) {
     __shared__ __attribute__((aligned(16))) RefineShared S;
-    const int r = blockIdx.y;
+    const int r = blockIdx.y;  // round of the R sets: r % n_r of its rows
     const int n = counts[r];
     const int groups = (n + kRefineGroup - 1) / kRefineGroup;
     if ((int)blockIdx.x >= groups) return;  // uniform per block
+    int32_t* buckets = buckets_ + r % n_r;
     const int* list = lists + list_stride * r;
     const float* Rt = r_t + (size_t)r * half_pad * kHeadDim;  // [column][t], zero columns up to half_pad
     const int lane = lane_id(), e16 = lane & 15, g16 = lane >> 4;
@@ -377,7 +384,7 @@ __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
                 const int oi = __shfl_xor(bi, o);
                 better(ov, oi, bv, bi);
             }
-            if (k == 0 && ei < n && ci >= 1 && ci <= kRefineCand) buckets[(int64_t)row * n_r + r] = bi;
+            if (k == 0 && ei < n && ci >= 1 && ci <= kRefineCand) buckets[(int64_t)row * n_r] = bi;
         }
 
         // entries left to fp64: every column, one wave each
@@ -406,7 +413,7 @@ __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
                 const int oi = __shfl_xor(bi, o);
                 better(ov, oi, bv, bi);
             }
-            if (lane == 0) buckets[(int64_t)list[ei] * n_r + r] = bi;
+            if (lane == 0) buckets[(int64_t)list[ei] * n_r] = bi;
         }
         __syncthreads();  // the group's LDS is reused by the next one
     }
@@ -692,8 +699,13 @@ constexpr uint16_t kUnsettled = 0xFFFFu;
 
 // The main kernel, one of three passes (MODE).  A wave owns 64 rows (two
 // 32-row blocks) and sweeps every staged tile once for them.
-//  * kScreen and kExact take rows blockIdx.x * 64 * WAVES + ... and all
-//    rounds; kListed takes, for round blockIdx.z, the rows the screen left
+//  * R comes in sets of n_r rounds: one set for all rows, or one per head
+//    (Slices).  The rows form slices that share a set; blocks are numbered
+//    slice after slice, so no block's rows span two sets.  Rounds count
+//    through the sets: round r of set s is s * n_r + r in the planes, norms,
+//    lists and counts.
+//  * kScreen and kExact take 64 * WAVES rows of one slice and all rounds of
+//    its set; kListed takes, for round blockIdx.z, the rows the screen left
 //    open in that round (its segments one after another), in chunks of
 //    64 * WAVES, workgroup blockIdx.x taking every gridDim.x-th chunk.
 //  * Every screened projection is within
@@ -711,14 +723,22 @@ constexpr uint16_t kUnsettled = 0xFFFFu;
 //    screen's lists are segmented, [round][kSegs][seg_cap] with counts
 //    [round][kSegs]; the exact passes' are [round][rows] with one count per
 //    round (few rows reach them).
+struct Slices {
+    int64_t rows;     // rows of a slice
+    int blocks;       // blocks of a slice
+    int sets;         // slices s, s + sets, ... share set s
+    int heads, head0; // slice s starts at row ((s / sets) heads + head0 + s % sets) rows
+    int64_t set_rows; // rows of a set, over all its slices (the stride of the exact passes' lists)
+};
+
 template <bool F32, int MODE, int WAVES, int ST>
 __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) void hash_kernel(
-    const void* __restrict__ q, int64_t rows, int n_r, int half, int half_pad,
-    const uint16_t* __restrict__ r_hi, const uint16_t* __restrict__ r_mid,
-    const float* __restrict__ col_norm_max, const float* __restrict__ res_max, float err_acc,
-    const float* __restrict__ res_max2, float err_acc2, float err_pack, const float* __restrict__ col_res,
+    const void* __restrict__ q, Slices sl, int n_r, int half, int half_pad,
+    const uint16_t* __restrict__ r_hi_, const uint16_t* __restrict__ r_mid_,
+    const float* __restrict__ col_norm_max_, const float* __restrict__ res_max_, float err_acc,
+    const float* __restrict__ res_max2_, float err_acc2, float err_pack, const float* __restrict__ col_res_,
     int32_t* __restrict__ buckets, const int* __restrict__ list_in,
-    const int* __restrict__ count_in, int* __restrict__ list_out, int* __restrict__ count_out,
+    const int* __restrict__ count_in, int* __restrict__ list_out_, int* __restrict__ count_out_,
     int64_t seg_cap) {
     static_assert(!F32 || MODE == kExact, "fp32 input takes the exact pass only");
     constexpr int NP = MODE == kScreen ? 1 : 2;
@@ -729,21 +749,33 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
     const int lane = tid & 63, h = lane >> 5, n = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t run_off = run_lane_offset(lane);
-    const uint32_t plane_bytes = (uint32_t)((size_t)n_r * half_pad * kHeadDim * 2);
+    // the slice of this block (kListed: unused) and its rows
+    const int slice = MODE == kListed ? 0 : (int)blockIdx.x / sl.blocks;
+    const int64_t slice_row = ((int64_t)(slice / sl.sets) * sl.heads + sl.head0 + slice % sl.sets) * sl.rows;
+    const int slice_block = MODE == kListed ? (int)blockIdx.x : (int)blockIdx.x % sl.blocks;
+    // this block's rounds of R: those of its set, or (kListed) the one round
+    // of blockIdx.z; everything per round is addressed from the first of them
+    const int64_t rr0 = MODE == kListed ? (int)blockIdx.z : slice % sl.sets * n_r;
+    const uint16_t *r_hi = r_hi_ + rr0 * half_pad * kHeadDim, *r_mid = r_mid_ + rr0 * half_pad * kHeadDim;
+    const float *col_norm_max = col_norm_max_ + rr0, *res_max = F32 ? nullptr : res_max_ + rr0;
+    const float *res_max2 = F32 ? nullptr : res_max2_ + rr0;
+    const float* col_res = MODE == kScreen ? col_res_ + rr0 * half_pad : nullptr;
+    int* list_out = list_out_ + rr0 * (MODE == kScreen ? kSegs * seg_cap : sl.set_rows);
+    int* count_out = count_out_ + rr0 * (MODE == kScreen ? kSegs : 1);
+    const int nrb = MODE == kListed ? 1 : n_r;  // rounds of this block
+    int32_t* bucket_cols = MODE == kListed ? buckets + (int)blockIdx.z % n_r : buckets;
+    const uint32_t plane_bytes = (uint32_t)((size_t)nrb * half_pad * kHeadDim * 2);
     const __amdgpu_buffer_rsrc_t rs_hi = plane_buffer(r_hi, plane_bytes), rs_mid = plane_buffer(r_mid, plane_bytes);
     using SG = Stage<NP, ST>;
     const int tpr = half_pad / 32;            // tiles per round
     const int spr = (tpr + ST - 1) / ST;      // stages per round
-    const int r_lo = MODE == kListed ? (int)blockIdx.z : 0;
-    const int r_end = MODE == kListed ? r_lo + 1 : n_r;
-    const int nrb = r_end - r_lo;  // rounds of this block
     // kListed: the round's open rows, segment after segment; lane s holds
     // the end of segment s in that sequence (kSegs is the wave width)
     int64_t listed = 0;
     int seg_end = 0;
     if constexpr (MODE == kListed) {
         static_assert(kSegs == 64, "one segment per lane");
-        int incl = count_in[(int64_t)r_lo * kSegs + lane];
+        int incl = count_in[rr0 * kSegs + lane];
         for (int o = 1; o < 64; o <<= 1) {
             const int y = __shfl_up(incl, o);
             if (lane >= o) incl += y;
@@ -753,7 +785,7 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
     }
     // kListed: the workgroups take the round's chunks of 64 * WAVES rows in
     // turn; the other passes take one chunk each.
-    for (int64_t chunk = blockIdx.x;; chunk += gridDim.x) {
+    for (int64_t chunk = slice_block;; chunk += gridDim.x) {
     if (MODE == kListed && chunk * (WAVES * kWaveRows) >= listed) break;  // uniform per block
     const int64_t slot0 = chunk * (WAVES * kWaveRows) + wave * kWaveRows;
     // the row of lane n of row block rb (lane half h keeps row block h's
@@ -771,18 +803,18 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
                 if (__shfl(seg_end, sg + step - 1) <= kk) sg += step;
             sg = min(sg, 63);
             const int before = __shfl(seg_end, max(sg - 1, 0));
-            const int64_t at = ((int64_t)r_lo * kSegs + sg) * seg_cap + (kk - (sg > 0 ? before : 0));
+            const int64_t at = (rr0 * kSegs + sg) * seg_cap + (kk - (sg > 0 ? before : 0));
             return valid ? list_in[at] : 0;
         } else {
-            valid = k < rows;
-            return valid ? k : 0;
+            valid = k < sl.rows;
+            return slice_row + (valid ? k : 0);
         }
     };
     // this wave's winners: [row in wave][round of the block]
     uint16_t* win = reinterpret_cast<uint16_t*>(smem + hash_win_offset(SG::kBytes, WAVES, nrb)) +
                     (size_t)wave * kWaveRows * nrb;
 
-    load_stage<WAVES, NP, ST>(smem, 0, r_lo * spr, spr, half_pad, rs_hi, rs_mid, wave, run_off);
+    load_stage<WAVES, NP, ST>(smem, 0, 0, spr, half_pad, rs_hi, rs_mid, wave, run_off);
 
     // Queries as the B operand: lane holds row (n) and k = 32h + 8s + e, s = 0..3.
     u32x4 qa[kRB][4];
@@ -865,9 +897,9 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
     // tiles, and the group the best key came from
     uint32_t best[kRB], second[kRB], grp_start[kRB];
     int best_grp[kRB];
-    const int g_end = r_end * spr;
-    for (int g = r_lo * spr; g < g_end; ++g) {
-        const int r = g / spr, st = g % spr, buf = (g - r_lo * spr) & 1;
+    const int g_end = nrb * spr;
+    for (int g = 0; g < g_end; ++g) {
+        const int r = g / spr, st = g % spr, buf = g & 1;
         if (st == 0) {
 #pragma unroll
             for (int rb = 0; rb < kRB; ++rb) {
@@ -936,7 +968,7 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
                     const float thr = 2.04f * (qn[rb] * (res + err_acc * cn) + err_pack * b1);
                     const bool flag = !(b1 - s1 > thr) || col[rb] >= half;
                     const int id = (bk[rb] & 1u) ? half + col[rb] : col[rb];
-                    if (rb == h) win[(rb * 32 + n) * nrb + (r - r_lo)] = flag ? kUnsettled : (uint16_t)id;
+                    if (rb == h) win[(rb * 32 + n) * nrb + r] = flag ? kUnsettled : (uint16_t)id;
                 }
             } else {
                 // x = q_row . R_col of the best key's column (fp32 sums of
@@ -987,7 +1019,7 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
                                                 : 1.02f * qn[rb] * (res_max2[r] + err_acc2 * cn);
                     const bool flag = !(fabsf(x) - eps_x > s1 * (1.f + 2.f * err_pack) + eps) || col[rb] >= half;
                     const int id = x < 0.f ? half + col[rb] : col[rb];
-                    if (rb == h) win[(rb * 32 + n) * nrb + (r - r_lo)] = flag ? kUnsettled : (uint16_t)id;
+                    if (rb == h) win[(rb * 32 + n) * nrb + r] = flag ? kUnsettled : (uint16_t)id;
                 }
             }
         }
@@ -1012,7 +1044,7 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
         for (int rr = 0; rr < nrb; ++rr) {
             const uint16_t id = w[rr];
             const bool queue = valid && id == kUnsettled;
-            if (valid) buckets[row * n_r + r_lo + rr] = id == kUnsettled ? 0 : (int32_t)id;
+            if (valid) bucket_cols[row * n_r + rr] = id == kUnsettled ? 0 : (int32_t)id;
             const uint64_t qmask = __ballot(queue);
             if (qmask) {
                 const int leader = __ffsll((unsigned long long)qmask) - 1;
@@ -1023,26 +1055,26 @@ __global__ __launch_bounds__(WAVES * 64, (MODE == kScreen ? kScreenOcc : 1)) voi
             }
         }
         __syncthreads();
-        const int64_t seg = blockIdx.x % kSegs;
-        if (tid < nrb) lbase[tid] = lcnt[tid] > 0 ? atomicAdd(&count_out[(int64_t)(r_lo + tid) * kSegs + seg], lcnt[tid]) : 0;
+        // blocks of a set go round its segments
+        const int64_t seg = ((int64_t)(slice / sl.sets) * sl.blocks + slice_block) % kSegs;
+        if (tid < nrb) lbase[tid] = lcnt[tid] > 0 ? atomicAdd(&count_out[(int64_t)tid * kSegs + seg], lcnt[tid]) : 0;
         __syncthreads();
         for (int rr = 0; rr < nrb; ++rr) {
-            int* dst = list_out + ((int64_t)(r_lo + rr) * kSegs + seg) * seg_cap + lbase[rr];
+            int* dst = list_out + ((int64_t)rr * kSegs + seg) * seg_cap + lbase[rr];
             for (int i = tid; i < lcnt[rr]; i += WAVES * 64) dst[i] = lq[rr * WAVES * kWaveRows + i];
         }
     } else {
         for (int rr = 0; rr < nrb; ++rr) {
-            const int r = r_lo + rr;
             const uint16_t id = w[rr];
             const bool queue = valid && id == kUnsettled;
-            if (valid) buckets[row * n_r + r] = id == kUnsettled ? 0 : (int32_t)id;
+            if (valid) bucket_cols[row * n_r + rr] = id == kUnsettled ? 0 : (int32_t)id;
             // wave-aggregated append to this round's list
             const uint64_t qmask = __ballot(queue);
             if (qmask) {
-                int* list = list_out + rows * r;
+                int* list = list_out + sl.set_rows * rr;
                 const int leader = __ffsll((unsigned long long)qmask) - 1;
                 int lslot = 0;
-                if (lane == leader) lslot = atomicAdd(&count_out[r], __popcll(qmask));
+                if (lane == leader) lslot = atomicAdd(&count_out[rr], __popcll(qmask));
                 lslot = __shfl(lslot, leader);
                 if (queue) list[lslot + __popcll(qmask & ((1ull << lane) - 1ull))] = (int)row;
             }
@@ -1060,7 +1092,6 @@ struct HashWs {
     float* col_norm;  // [3][n_r][half_pad]: |R_c|, |R_c - hi_c|, |R_c - hi_c - mid_c|
     float* norm_max;  // [3][n_r]: the largest of each
     int* r_exp;       // [n_r]: binary16 planes hold R * 2^r_exp (bf16 input)
-    float* r_part;    // [n_r][kScaleParts]: partial maxima of |R|
     int* count;       // [n_r][kSegs] rows left open by the screen, then [n_r] by the exact passes
     int* list1;       // [n_r][kSegs][seg_cap]
     int* list2;       // [n_r][rows]
@@ -1071,9 +1102,9 @@ struct HashWs {
 constexpr int kHashWaves = 4;
 constexpr int64_t kRowsPerBlock = kHashWaves * 64;
 
-HashWs carve(void* base, int64_t rows, int n_rounds, int half_pad) {
+// n_rounds: the rounds of all sets; rows, blocks: those of one set.
+HashWs carve(void* base, int64_t rows, int64_t blocks, int n_rounds, int half_pad) {
     const size_t per = (size_t)n_rounds * half_pad * kHeadDim;
-    const int64_t blocks = (rows + kRowsPerBlock - 1) / kRowsPerBlock;
     char* p = static_cast<char*>(base);
     HashWs w{};
     w.seg_cap = (blocks + kSegs - 1) / kSegs * kRowsPerBlock;
@@ -1090,8 +1121,6 @@ HashWs carve(void* base, int64_t rows, int n_rounds, int half_pad) {
     off += align256((size_t)3 * n_rounds * 4);
     w.r_exp = reinterpret_cast<int*>(p + off);
     off += align256((size_t)n_rounds * 4);
-    w.r_part = reinterpret_cast<float*>(p + off);
-    off += align256((size_t)n_rounds * kScaleParts * 4);
     w.count = reinterpret_cast<int*>(p + off);
     off += align256((size_t)n_rounds * (kSegs + 1) * 4);
     w.list1 = reinterpret_cast<int*>(p + off);
@@ -1105,7 +1134,7 @@ HashWs carve(void* base, int64_t rows, int n_rounds, int half_pad) {
 // Arguments of one pass of hash_kernel.
 struct PassArgs {
     const void* q;
-    int64_t rows;
+    Slices slices;
     int n_r, half, half_pad;
     const uint16_t *r_hi, *r_mid;
     const float *cn_max, *res;
@@ -1125,7 +1154,7 @@ void launch_pass_st(const PassArgs& a, dim3 grid, int rounds, hipStream_t stream
     const size_t lds = hash_win_offset(Stage<NP, ST>::kBytes, WAVES, rounds) + (size_t)WAVES * 64 * rounds * 2;
     auto* k = &hash_kernel<F32, MODE, WAVES, ST>;
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    k<<<grid, WAVES * 64, lds, stream>>>(a.q, a.rows, a.n_r, a.half, a.half_pad, a.r_hi, a.r_mid, a.cn_max, a.res,
+    k<<<grid, WAVES * 64, lds, stream>>>(a.q, a.slices, a.n_r, a.half, a.half_pad, a.r_hi, a.r_mid, a.cn_max, a.res,
                                          a.err_acc, a.res2, a.err_acc2, a.err_pack, a.col_res, a.buckets, a.list_in,
                                          a.count_in, a.list_out, a.count_out, a.seg_cap);
 }
@@ -1154,33 +1183,58 @@ void launch_pass(const PassArgs& a, dim3 grid, int rounds, hipStream_t stream) {
 
 }  // namespace
 
-size_t hash_workspace_bytes(int64_t rows, int n_rounds, int n_buckets) {
-    const int half_pad = (n_buckets / 2 + 31) / 32 * 32;
-    return carve(nullptr, rows, n_rounds, half_pad).bytes;
+namespace {
+
+// How a call's rows fall into slices and R sets.  With one R per head, the
+// heads are hashed together, up to kMaxRounds rounds of R at a time (which
+// bounds the planes' workspace at 256 MiB).
+constexpr int kMaxSetRounds = 1024;
+
+Slices slices_of(int64_t BH, int L, int heads, int n_rounds) {
+    Slices s{};
+    if (heads == 0) {  // one R
+        s.rows = BH * L;
+        s.heads = s.sets = 1;
+        s.set_rows = s.rows;
+    } else {
+        s.rows = L;
+        s.heads = heads;
+        s.sets = std::min(heads, std::max(1, kMaxSetRounds / n_rounds));
+        s.set_rows = BH / heads * L;
+    }
+    s.blocks = (int)((s.rows + kRowsPerBlock - 1) / kRowsPerBlock);
+    return s;
 }
 
-hipError_t launch_hash(const void* q, bool f32, int64_t rows, int n_rounds, int n_buckets,
-                       const float* R, int32_t* buckets, void* workspace, hipStream_t stream) {
-    const int half = n_buckets / 2;
-    const int half_pad = (half + 31) / 32 * 32;
-    const HashWs w = carve(workspace, rows, n_rounds, half_pad);
-    const float* cn_max = w.norm_max;                       // max |R_c|
-    const float* res1_max = w.norm_max + n_rounds;          // max |R_c - hi_c|
-    const float* res2_max = w.norm_max + 2 * n_rounds;      // max |R_c - hi_c - mid_c|
-    int* count1 = w.count;                                  // [n_r][kSegs]: left open by the screen
-    int* count2 = w.count + (size_t)n_rounds * kSegs;       // [n_r]: left to the fp64 refinement
+HashWs carve(void* base, const Slices& s, int n_rounds, int half_pad) {
+    return carve(base, s.set_rows, s.set_rows / s.rows * s.blocks, s.sets * n_rounds, half_pad);
+}
 
-    if (f32) {
-        prep_r_cols_kernel<false><<<dim3(half_pad, n_rounds), 64, 0, stream>>>(
-            R, half, half_pad, nullptr, nullptr, w.r_hi, w.r_mid, w.r_t, w.col_norm);
-    } else {
-        prep_r_part_kernel<<<dim3(kScaleParts, n_rounds), 256, 0, stream>>>(R, half, w.r_part);
-        prep_r_cols_kernel<true><<<dim3(half_pad, n_rounds), 64, 0, stream>>>(
-            R, half, half_pad, w.r_part, w.r_exp, w.r_hi, w.r_mid, w.r_t, w.col_norm);
-    }
-    prep_r_max_kernel<<<dim3(n_rounds, 3), 256, 0, stream>>>(w.col_norm, n_rounds, half_pad, w.norm_max,
-                                                             w.count, n_rounds * (kSegs + 1));
-    if (rows == 0) return hipGetLastError();
+template <bool F16>
+void launch_prep(const float* R, int rounds, int half, int half_pad, const HashWs& w, hipStream_t stream) {
+    const int blocks = (half_pad + kPrepCols - 1) / kPrepCols;
+    prep_r_kernel<F16><<<dim3(blocks, rounds), kPrepThreads, 0, stream>>>(
+        R, half, half_pad, w.r_exp, w.r_hi, w.r_mid, w.r_t, w.col_norm, w.norm_max, w.count, kSegs,
+        w.count + (size_t)rounds * kSegs);
+    if (blocks > 1) prep_r_max_kernel<<<dim3(rounds, 3), 512, 0, stream>>>(w.col_norm, rounds, half_pad, w.norm_max);
+}
+
+// Hash the slices of `sl` (all heads, or a group of them; `all` sizes the
+// workspace) with their R sets.
+hipError_t launch_hash_sets(const void* q, bool f32, const Slices& sl, const Slices& all, int n_rounds, int half,
+                            int half_pad, const float* R, int32_t* buckets, void* workspace, hipStream_t stream) {
+    const int rounds = sl.sets * n_rounds;
+    HashWs w = carve(workspace, all, n_rounds, half_pad);
+    R += (size_t)sl.head0 * n_rounds * kHeadDim * half;
+    const float* cn_max = w.norm_max;                  // max |R_c|
+    const float* res1_max = w.norm_max + rounds;       // max |R_c - hi_c|
+    const float* res2_max = w.norm_max + 2 * rounds;   // max |R_c - hi_c - mid_c|
+    int* count1 = w.count;                             // [rounds][kSegs]: left open by the screen
+    int* count2 = w.count + (size_t)rounds * kSegs;    // [rounds]: left to the fp64 refinement
+    if (f32)
+        launch_prep<false>(R, rounds, half, half_pad, w, stream);
+    else
+        launch_prep<true>(R, rounds, half, half_pad, w, stream);
 
     // Error of a screened key against the exact |projection| p_c, beyond the
     // planes' residual q . (R_c - planes) <= |q| |R_c - planes|:
@@ -1199,25 +1253,26 @@ hipError_t launch_hash(const void* q, bool f32, int64_t rows, int n_rounds, int 
     const float acc_f32 = (float)((3.1 * 0x1p-16 + 3 * kHeadDim * 0x1p-23) * 1.01);
 
     constexpr int kWaves = kHashWaves;
-    const unsigned grid = (unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock);
+    const int64_t n_slices = sl.set_rows / sl.rows * sl.sets;
+    const unsigned grid = (unsigned)(n_slices * sl.blocks);
     // Refinement blocks: about two per CU over all rounds.  A typical list holds
     // 0.1% of the rows (64 groups of 16 at 1M rows); longer lists are strided,
     // and a block keeps its R for all of its groups.
     const unsigned refine_blocks = (unsigned)std::max<int64_t>(
-        1, std::min<int64_t>(std::max(1, 512 / n_rounds), (rows + kRefineGroup - 1) / kRefineGroup));
+        1, std::min<int64_t>(std::max(1, 512 / rounds), (sl.set_rows + kRefineGroup - 1) / kRefineGroup));
     if (f32) {
         launch_pass<true, kExact, kWaves>(
-            PassArgs{q, rows, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, nullptr, acc_f32, nullptr, 0.f,
+            PassArgs{q, sl, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, nullptr, acc_f32, nullptr, 0.f,
                      err_pack, nullptr, buckets, nullptr, nullptr, w.list2, count2, 0},
             dim3(grid), n_rounds, stream);
-        hash_refine_kernel<true><<<dim3(refine_blocks, n_rounds), kRefineThreads, 0, stream>>>(
-            q, w.r_t, half, half_pad, n_rounds, rows, w.list2, count2, cn_max, nullptr, buckets);
+        hash_refine_kernel<true><<<dim3(refine_blocks, rounds), kRefineThreads, 0, stream>>>(
+            q, w.r_t, half, half_pad, n_rounds, sl.set_rows, w.list2, count2, cn_max, nullptr, buckets);
     } else {
         // screen with R's hi plane; the rows it leaves open get both planes;
         // what those leave open gets the fp64 refinement
         launch_pass<false, kScreen, kWaves>(
-            PassArgs{q, rows, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, res1_max, acc1, res2_max, acc2,
-                     err_pack, w.col_norm + (size_t)n_rounds * half_pad, buckets, nullptr, nullptr, w.list1, count1,
+            PassArgs{q, sl, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, res1_max, acc1, res2_max, acc2,
+                     err_pack, w.col_norm + (size_t)rounds * half_pad, buckets, nullptr, nullptr, w.list1, count1,
                      w.seg_cap},
             dim3(grid), n_rounds, stream);
         // Four waves a workgroup.  Deciding from the hi plane alone, the
@@ -1226,15 +1281,42 @@ hipError_t launch_hash(const void* q, bool f32, int64_t rows, int n_rounds, int 
         // rows; longer lists loop.
         constexpr int kListedWaves = 4;
         const int64_t listed_rows = kListedWaves * 64;
-        const unsigned per_round = (unsigned)std::min<int64_t>(128, (rows + listed_rows - 1) / listed_rows);
+        const unsigned per_round = (unsigned)std::min<int64_t>(std::min(128, std::max(4, 1024 / rounds)),
+                                                               (sl.set_rows + listed_rows - 1) / listed_rows);
         launch_pass<false, kListed, kListedWaves>(
-            PassArgs{q, rows, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, res2_max, acc2, res2_max, acc2,
+            PassArgs{q, sl, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, res2_max, acc2, res2_max, acc2,
                      err_pack, nullptr, buckets, w.list1, count1, w.list2, count2, w.seg_cap},
-            dim3(per_round, 1, n_rounds), 1, stream);
-        hash_refine_kernel<false><<<dim3(refine_blocks, n_rounds), kRefineThreads, 0, stream>>>(
-            q, w.r_t, half, half_pad, n_rounds, rows, w.list2, count2, cn_max, w.r_exp, buckets);
+            dim3(per_round, 1, rounds), 1, stream);
+        hash_refine_kernel<false><<<dim3(refine_blocks, rounds), kRefineThreads, 0, stream>>>(
+            q, w.r_t, half, half_pad, n_rounds, sl.set_rows, w.list2, count2, cn_max, w.r_exp, buckets);
     }
     return hipGetLastError();
+}
+
+}  // namespace
+
+size_t hash_workspace_bytes(int64_t BH, int L, int heads, int n_rounds, int n_buckets) {
+    const int half_pad = (n_buckets / 2 + 31) / 32 * 32;
+    return carve(nullptr, slices_of(BH, L, heads, n_rounds), n_rounds, half_pad).bytes;
+}
+
+hipError_t launch_hash(const void* q, bool f32, int64_t BH, int L, int heads, int n_rounds, int n_buckets,
+                       const float* R, int32_t* buckets, void* workspace, hipStream_t stream) {
+    const int half = n_buckets / 2;
+    const int half_pad = (half + 31) / 32 * 32;
+    if (BH == 0 || L == 0) return hipSuccess;
+    Slices sl = slices_of(BH, L, heads, n_rounds);
+    if (sl.head0 + sl.sets < sl.heads) {  // groups of heads, one after another
+        for (int h = 0; h < heads; h += sl.sets) {
+            Slices part = sl;
+            part.head0 = h;
+            part.sets = std::min(sl.sets, heads - h);
+            const hipError_t e = launch_hash_sets(q, f32, part, sl, n_rounds, half, half_pad, R, buckets, workspace, stream);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    return launch_hash_sets(q, f32, sl, sl, n_rounds, half, half_pad, R, buckets, workspace, stream);
 }
 
 }  // namespace lsh

@@ -20,8 +20,10 @@ constexpr int kHeadDimHost = 64;  // d_k the kernels are specialised for
 constexpr int kChunkHost = 64;    // chunk length m the kernels are specialised for
 
 // ---- hashing ----
-size_t hash_workspace_bytes(int64_t rows, int n_rounds, int n_buckets);
-hipError_t launch_hash(const void* q, bool f32, int64_t rows, int n_rounds, int n_buckets,
+// heads: 0 for one R over all rows, else the head count H of one R per head
+// (R [H][n_rounds][d][n_buckets/2], slice bh hashed with set bh % H).
+size_t hash_workspace_bytes(int64_t BH, int L, int heads, int n_rounds, int n_buckets);
+hipError_t launch_hash(const void* q, bool f32, int64_t BH, int L, int heads, int n_rounds, int n_buckets,
                        const float* R, int32_t* buckets, void* workspace, hipStream_t stream);
 
 // ---- counting sort and row gather ----

@@ -49,6 +49,12 @@ int check_supported(const lsh_config* cfg) {
 
 int64_t bh_of(const lsh_config* cfg) { return (int64_t)cfg->B * cfg->H; }
 
+// R sets of a hash: 0 for one R over all rows, else one per head.
+int hash_heads(const lsh_config* cfg) { return cfg->r_per_head ? cfg->H : 0; }
+size_t hash_bytes(const lsh_config* cfg) {
+    return lsh::hash_workspace_bytes(bh_of(cfg), cfg->L, hash_heads(cfg), cfg->n_rounds, cfg->n_buckets);
+}
+
 // The attention entry points need self_mask >= kMinSelfMask.
 int check_self_mask(const lsh_config* cfg) {
     return cfg->self_mask >= kMinSelfMask ? LSH_OK : LSH_ERR_UNSUPPORTED;
@@ -148,7 +154,7 @@ size_t lsh_workspace_bytes(const lsh_config* cfg, lsh_dtype dtype, int op) {
     }
     if (check_config(cfg) != LSH_OK || check_dtype(dtype) != LSH_OK) return 0;
     const int64_t BH = bh_of(cfg);
-    const size_t hash = lsh::hash_workspace_bytes(BH * cfg->L, cfg->n_rounds, cfg->n_buckets);
+    const size_t hash = hash_bytes(cfg);
     const size_t sort = lsh::sort_workspace_bytes(BH, cfg->L, cfg->n_rounds, cfg->n_buckets);
     switch (op) {
         case LSH_OP_HASH: return hash;
@@ -171,27 +177,10 @@ int lsh_hash(const lsh_config* cfg, lsh_dtype dtype, const void* q, const float*
     LSH_TRY(check_dtype(dtype));
     if (!q || !R || !buckets || !workspace) return LSH_ERR_INVALID;
     if (!all_aligned(q, R, workspace)) return LSH_ERR_INVALID;
-    if (workspace_bytes < lsh::hash_workspace_bytes(bh_of(cfg) * cfg->L, cfg->n_rounds, cfg->n_buckets))
-        return LSH_ERR_INVALID;
+    if (workspace_bytes < hash_bytes(cfg)) return LSH_ERR_INVALID;
     LSH_TRY(check_supported(cfg));
-    const hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool f32 = dtype == LSH_F32;
-    if (!cfg->r_per_head) {
-        const int64_t rows = bh_of(cfg) * cfg->L;
-        return status_of(lsh::launch_hash(q, f32, rows, cfg->n_rounds, cfg->n_buckets, R, buckets,
-                                          workspace, st));
-    }
-    // one R per head: every (batch, head) slice is hashed with its head's R,
-    // slice by slice (the slices share nothing, and each pass needs one R)
-    const size_t r_set = (size_t)cfg->n_rounds * cfg->d * (cfg->n_buckets / 2);
-    const size_t row_bytes = (size_t)cfg->d * elem_bytes(dtype);
-    for (int64_t bh = 0; bh < bh_of(cfg); ++bh) {
-        const int64_t row0 = bh * cfg->L;
-        LSH_TRY(status_of(lsh::launch_hash(static_cast<const char*>(q) + row0 * row_bytes, f32, cfg->L,
-                                           cfg->n_rounds, cfg->n_buckets, R + (bh % cfg->H) * r_set,
-                                           buckets + row0 * cfg->n_rounds, workspace, st)));
-    }
-    return LSH_OK;
+    return status_of(lsh::launch_hash(q, dtype == LSH_F32, bh_of(cfg), cfg->L, hash_heads(cfg), cfg->n_rounds,
+                                      cfg->n_buckets, R, buckets, workspace, static_cast<hipStream_t>(stream)));
 }
 
 int lsh_sort_permute(const lsh_config* cfg, const int32_t* buckets, int32_t* perm, int32_t* undo,

@@ -46,3 +46,19 @@ def test_hash_close_columns(gpu, dtype, L, n_buckets, copies, k):
     log("hash-close", dtype, L, n_buckets, copies, k)
     got = lsh.lsh_hash(lsh.Config.of(w), to_device(qin, dtype), to_device(R, "f32")).cpu().numpy()
     assert np.array_equal(got, want)
+
+
+# One R per head: slices that end inside a workgroup's rows (L = 1, 255, 300),
+# one head, and more rounds of R than are hashed together (H n_rounds = 1040).
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H,L,n_r,n_buckets", [(2, 3, 300, 2, 66), (3, 1, 255, 1, 2), (1, 65, 40, 16, 34),
+                                                 (5, 2, 1, 3, 1022), (2, 2, 512, 4, 256)])
+def test_hash_per_head_slices(gpu, dtype, B, H, L, n_r, n_buckets):
+    w = small("causal_bf16_L16384", B=B, H=H, L=L, n_buckets=n_buckets, n_rounds=n_r, dtype=dtype)
+    x = W.make_inputs(w)
+    R = np.random.default_rng(7).standard_normal((H, n_r, 64, n_buckets // 2), dtype=np.float32)
+    want, _ = oracle.lsh_hash(W.as_f64(x["q"], dtype), R.astype(np.float64))
+    log("hash-per-head", dtype, B, H, L, n_r, n_buckets)
+    cfg = lsh.Config.of(w, r_per_head=True)
+    got = lsh.lsh_hash(cfg, to_device(x["q"], dtype), to_device(R, "f32")).cpu().numpy()
+    assert np.array_equal(got, want)
