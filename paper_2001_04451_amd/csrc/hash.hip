@@ -1161,11 +1161,11 @@ void launch_pass_st(const PassArgs& a, dim3 grid, int rounds, hipStream_t stream
 
 // Tiles per stage: the round's tile count rounded up to a power of two, at
 // most kScreenMaxTiles for the screen (one plane), 8 for the fp32 pass (two
-// planes) and 2 for the listed pass (two planes: 240 registers, two waves a
+// planes) and 2 for bf16 input's two planes (240 registers, two waves a
 // SIMD; four tiles take 337, one wave a SIMD, and were slower).
 template <bool F32, int MODE, int WAVES>
 void launch_pass(const PassArgs& a, dim3 grid, int rounds, hipStream_t stream) {
-    constexpr int kMax = MODE == kScreen ? kScreenMaxTiles : (MODE == kListed ? 2 : 8);
+    constexpr int kMax = MODE == kScreen ? kScreenMaxTiles : (F32 ? 8 : 2);
     const int tpr = a.half_pad / 32;
     if (tpr <= 1)
         launch_pass_st<F32, MODE, WAVES, 1>(a, grid, rounds, stream);
@@ -1189,6 +1189,13 @@ namespace {
 // heads are hashed together, up to kMaxRounds rounds of R at a time (which
 // bounds the planes' workspace at 256 MiB).
 constexpr int kMaxSetRounds = 1024;
+
+// bf16 calls of at most this many projections (rows x rounds x columns) take
+// both planes of R at once: twice the products, but no pass over the rows a
+// screen leaves open, which costs 10 us however few they are.  Whole hash,
+// one pass against screen and listed pass: 30.4 / 38.3 us at 8 M projections,
+// 39.2 / 43.3 at 32 M, 65.9 / 58.8 at 72 M, 78.7 / 70.2 at 128 M.
+constexpr int64_t kSmallProjections = (int64_t)40 << 20;
 
 Slices slices_of(int64_t BH, int L, int heads, int n_rounds) {
     Slices s{};
@@ -1267,6 +1274,14 @@ hipError_t launch_hash_sets(const void* q, bool f32, const Slices& sl, const Sli
             dim3(grid), n_rounds, stream);
         hash_refine_kernel<true><<<dim3(refine_blocks, rounds), kRefineThreads, 0, stream>>>(
             q, w.r_t, half, half_pad, n_rounds, sl.set_rows, w.list2, count2, cn_max, nullptr, buckets);
+    } else if (sl.set_rows * sl.sets * n_rounds * half_pad <= kSmallProjections) {
+        // both planes at once
+        launch_pass<false, kExact, kWaves>(
+            PassArgs{q, sl, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, res2_max, acc2, res2_max, acc2,
+                     err_pack, nullptr, buckets, nullptr, nullptr, w.list2, count2, 0},
+            dim3(grid), n_rounds, stream);
+        hash_refine_kernel<false><<<dim3(refine_blocks, rounds), kRefineThreads, 0, stream>>>(
+            q, w.r_t, half, half_pad, n_rounds, sl.set_rows, w.list2, count2, cn_max, w.r_exp, buckets);
     } else {
         // screen with R's hi plane; the rows it leaves open get both planes;
         // what those leave open gets the fp64 refinement
