@@ -10,15 +10,22 @@
 // Products: C = A W^T with A the activations (rows of K bf16 values, or the
 // attention's output in its [B, H, L, 64] layout) and W a weight matrix
 // [N][K] in bf16, fp32 accumulation on the matrix cores
-// (mfma_f32_16x16x32_bf16).  A workgroup of four waves computes a 128 x 128
-// tile of C; each wave a 64 x 64 quarter as 4 x 4 products of 16 x 16 with W
-// as the first operand, so a lane ends up with four consecutive output
-// columns of one row.  A and W tiles of 128 rows x 64 k stream through LDS by
-// buffer loads straight into LDS, double-buffered, one barrier per k-tile;
-// piece p (16 B) of tile row r sits at slot p ^ (r & 7), so the 16 rows an
-// operand load reads hit distinct banks.  Rows past M read as zero (the
-// buffer's bound) and are not stored.  Workgroups are numbered so that the N
-// tiles of one row tile run on one XCD, which then reads those rows of A from
+// (mfma_f32_16x16x32_bf16), W as the first operand (a lane ends up with four
+// consecutive output columns of one row).  A workgroup of four waves computes
+// a square tile of C of 256, 128 or 64 (by the tile count, launch_gemm); A
+// and W pass through a ring of LDS stages of 64 k-values, copied there by
+// buffer loads and counted by hand, and each wave holds the next stage's
+// operands in registers by the time it needs them: one barrier a stage, no
+// wait on an LDS read.  What bounded the earlier kernel (128 x 128, two
+// buffers, operands read when needed; 650-750 TFLOP/s) was the copies: 64
+// bytes a cycle into a CU are as long as the products of a 128 x 128 tile.  A
+// 256 x 256 tile needs half of that; its single wave per SIMD then must not
+// issue anything in a row, so every copy and operand read stands alone between
+// two products.  16384 x 1024 x 4096 with residual: 185 -> 128 us (1.07
+// PFLOP/s), 16384 x 4096 x 1024 to bf16: 209 -> 167 us, 65536 x 1024 x 1024
+// with residual (0.67 GB): 321 -> 233 us; 4095 x 512 x 2048: 38 -> 17 us.
+// Workgroups are numbered so that an XCD works on a block of row and column
+// tiles at a time and reads their rows of A and W from
 // memory once.  The epilogue adds the bias and either
 //  * adds the product, times a sign, to an fp32 residual (the branch outputs:
 //    y = x + F or x = y - F),
@@ -26,6 +33,8 @@
 //  * stores bf16 q or v in the attention's [B, H, L, 64] layout.
 #include "attn_common.h"
 #include "launch.h"
+
+#include <type_traits>
 
 namespace lsh {
 namespace {
@@ -81,19 +90,6 @@ __global__ __launch_bounds__(256) void layer_norm_kernel(const float* __restrict
 // ---------------------------------------------------------------------------
 // Products
 
-constexpr int kTile = 128;                 // rows of A and of W per workgroup
-constexpr int kBK = 64;                    // k per LDS tile
-constexpr uint32_t kTileBytes = kTile * kBK * 2;
-constexpr int kGemmThreads = 256;
-
-// Raw buffer (word 3: raw, untyped 32-bit data); loads past num_records read 0.
-constexpr int kRawBufferWord3 = 0x00020000;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const void* p, uint64_t bytes) {
-    const uint32_t n = bytes >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)n, kRawBufferWord3);
-}
-
 enum : int { kInRows = 0, kInHeads = 1 };                    // A layout
 enum : int { kOutResid = 0, kOutReluBf16 = 1, kOutHeads = 2 };  // epilogue
 
@@ -110,137 +106,301 @@ struct GemmArgs {
     uint16_t* out_bf16;     // kOutReluBf16: [M][N]; kOutHeads: [B][H][L][64]
 };
 
-template <int IN, int OUT>
-__global__ __launch_bounds__(kGemmThreads, 2) void gemm_bf16_kernel(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) char sa[2][kTileBytes];
-    __shared__ __attribute__((aligned(16))) char sw[2][kTileBytes];
+// Raw buffer descriptor (word 3: raw, untyped 32-bit data).
+__device__ __forceinline__ u32x4 raw_buffer(const void* p, uint64_t bytes) {
+    const uint64_t a = (uint64_t)p;
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), bytes >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes, 0x00020000u};
+}
 
+// 16 bytes per lane from the buffer at byte v_off + s_off straight to LDS at
+// lds + 16 * lane.  Inline assembly, so that the compiler neither orders LDS
+// reads behind it nor waits for it: the kernel counts its own loads.
+__device__ __forceinline__ void buffer_to_lds(u32x4 buf, uint32_t v_off, uint32_t s_off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(v_off), "s"(buf), "s"(s_off), "s"(lds)
+                 : "memory", "m0");
+}
+
+// Shape of one product kernel: a workgroup of four waves computes a TM x TN
+// tile of C, each wave a quarter of TM / 2 x TN / 2 as 16 x 16 products.  A and
+// W pass through LDS in stages of KB k-values, STAGES of them in flight.
+template <int TM_, int TN_, int KB_, int STAGES_>
+struct GemmShape {
+    static constexpr int TM = TM_, TN = TN_, KB = KB_, STAGES = STAGES_;
+    static constexpr int kPieces = KB / 8;             // 16-byte pieces per row
+    static constexpr int kRowBytes = 2 * KB;
+    static constexpr int kRunRows = 64 / kPieces;      // rows one copy instruction fills
+    static constexpr int kStageBytes = (TM + TN) * kRowBytes;
+    static constexpr int kLoadsA = TM / kRunRows / 4, kLoadsW = TN / kRunRows / 4;  // per wave and stage
+    static constexpr int kLoads = kLoadsA + kLoadsW;
+    static constexpr int MI = TM / 32, NI = TN / 32;   // 16-row blocks per wave
+    static constexpr int KS = KB / 32;                 // k-steps per stage
+    static constexpr size_t kLds = (size_t)STAGES * kStageBytes;
+    // Slot of piece p of a row.  The LDS serves a 16-byte read in groups of
+    // sixteen lanes, 0-3, 12-15, 20-23 and 24-27 the first of them (inferred
+    // from SQ_LDS_BANK_CONFLICT under several layouts); under these slots a
+    // group's rows and pieces meet all 64 banks once: no conflicts counted.
+    static __device__ __forceinline__ int slot(int row, int p) { return KB == 32 ? p ^ (-(row >> 2) & 3) : p ^ (row & 7); }
+};
+
+// Until at most N of the wave's loads are in flight and its LDS reads are
+// done (as the builtin, so that the compiler knows of the latter).
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+    static_assert(N < 64, "vmcnt has six bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+    asm volatile("" ::: "memory");
+}
+
+// acc += a b, in place in the accumulation registers.  Inline assembly ties
+// the result to the accumulator's registers: with the builtin the allocator
+// gives results other registers than their addends and moves them back (350
+// moves beside the 128 products of two stages at 256 accumulators a lane).
+__device__ __forceinline__ void mfma_into(f32x4& acc, bf16x8 a, bf16x8 b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+
+// Workgroup barrier alone (no wait for copies in flight); no LDS access moves
+// across it.
+__device__ __forceinline__ void barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <class S, int IN, int OUT>
+__global__ __launch_bounds__(256, (S::kLds > 80 * 1024 ? 1 : 2)) void gemm_bf16_kernel(GemmArgs g) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // tile of this workgroup: N tiles of one row tile on one XCD when the
-    // tile count allows (workgroup b runs on XCD b % 8)
-    const int nN = g.N / kTile;
-    const int64_t nM = (g.M + kTile - 1) / kTile;
-    const int64_t T = nN * nM;
-    int64_t t = blockIdx.x;
-    if (T % 8 == 0) t = (t % 8) * (T / 8) + t / 8;
-    const int64_t m0 = (t / nN) * kTile;
-    const int n0 = (int)(t % nN) * kTile;
-    const int KT = g.K / kBK;
 
-    // Loads: wave w moves LDS rows 32w .. 32w+31 of both tiles, 8 rows per
-    // instruction; lane l fills row 8j + l/8, slot l%8 with piece
-    // (l%8) ^ (l/8) of that row (the row's low three bits are l/8).
-    const int lr = lane >> 3;
-    const uint32_t lp = (uint32_t)((lane & 7) ^ lr);
-    const __amdgpu_buffer_rsrc_t ra = raw_buffer(g.a, (uint64_t)g.M * g.K * 2);
-    const __amdgpu_buffer_rsrc_t rw = raw_buffer(g.w, (uint64_t)g.N * g.K * 2);
-    uint32_t a_off[4], w_off[4];  // byte offsets of the lane's piece at k-tile 0
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int r = 32 * wave + 8 * j + lr;
-        const int64_t m = m0 + r;
-        if constexpr (IN == kInRows) {
-            a_off[j] = m < g.M ? (uint32_t)((m * g.K + 8 * lp) * 2) : 0xFFFFFFF0u;
+    // Tile of this workgroup (workgroup b runs on XCD b % 8): each XCD owns a
+    // run of row tiles and walks it four columns of tiles at a time, so that
+    // the tiles in flight on it share rows of A and of W in its L2.
+    const int nN = g.N / S::TN;
+    const int nM = (int)((g.M + S::TM - 1) / S::TM);
+    int tm, tn;
+    {
+        const int t = blockIdx.x;
+        if (nM % 8 == 0) {
+            const int mx = nM / 8, u = t / 8;  // row tiles per XCD, place in the XCD's walk
+            const int gn = nN % 4 == 0 ? 4 : (nN % 2 == 0 ? 2 : 1);
+            tm = (t % 8) * mx + u / gn % mx;
+            tn = u / (gn * mx) * gn + u % gn;
         } else {
-            const int64_t bb = m / g.L, l = m % g.L;
-            a_off[j] = m < g.M ? (uint32_t)(((bb * g.H * g.L + l) * 64 + 8 * lp) * 2) : 0xFFFFFFF0u;
+            tm = t / nN;
+            tn = t % nN;
         }
-        w_off[j] = (uint32_t)(((int64_t)(n0 + r) * g.K + 8 * lp) * 2);
     }
-    // advance per k-tile: 64 values along a row, or one head
-    const uint32_t a_step = IN == kInRows ? kBK * 2 : (uint32_t)g.L * 64 * 2;
-    auto load_tiles = [&](int kt, int buf) {
+    const int64_t m0 = (int64_t)tm * S::TM;
+    const int n0 = tn * S::TN;
+    const int n_st = g.K / S::KB;
+
+    // Copies: lane l of a copy fills slot l % kPieces of row l / kPieces of a
+    // run of kRunRows rows.  Rows past M repeat the last row (not stored).
+    const u32x4 buf_a = raw_buffer(g.a, (uint64_t)g.M * g.K * 2), buf_w = raw_buffer(g.w, (uint64_t)g.N * g.K * 2);
+    uint32_t off[S::kLoads];
+    const int lrow = lane / S::kPieces, lslot = lane % S::kPieces;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int chunk = 4 * wave + j;  // 1 KB chunk: rows 8 chunk .. 8 chunk + 7
-            const uint32_t ao = a_off[j] == 0xFFFFFFF0u ? 0xFFFFFFF0u : a_off[j] + (uint32_t)kt * a_step;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(sa[buf] + 1024 * chunk),
-                                                     16, ao, 0, 0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(sw[buf] + 1024 * chunk),
-                                                     16, w_off[j] + (uint32_t)kt * (kBK * 2), 0, 0, 0);
-        }
+    for (int j = 0; j < S::kLoadsA; ++j) {
+        const int r = (wave * S::kLoadsA + j) * S::kRunRows + lrow;
+        const int64_t m = min(m0 + r, g.M - 1);
+        const uint32_t piece = 16u * (uint32_t)S::slot(r, lslot);
+        if constexpr (IN == kInRows)
+            off[j] = (uint32_t)(m * g.K * 2) + piece;
+        else
+            off[j] = (uint32_t)((m / g.L * g.H * g.L + m % g.L) * 128) + piece;
+    }
+#pragma unroll
+    for (int j = 0; j < S::kLoadsW; ++j) {
+        const int r = (wave * S::kLoadsW + j) * S::kRunRows + lrow;
+        off[S::kLoadsA + j] = (uint32_t)((int64_t)(n0 + r) * g.K * 2) + 16u * (uint32_t)S::slot(r, lslot);
+    }
+    const uint32_t lds0 = lds_addr(smem);
+    // copy j of stage st (into ring slot `ring`)
+    auto load = [&](int st, int ring, int j) {
+        const bool is_a = j < S::kLoadsA;
+        uint32_t k_off;  // bytes along k: a head is 64 k-values
+        if (IN == kInHeads && is_a)
+            k_off = S::KB == 64 ? (uint32_t)st * (uint32_t)g.L * 128u
+                                : (uint32_t)(st >> 1) * (uint32_t)g.L * 128u + (uint32_t)(st & 1) * 64u;
+        else
+            k_off = (uint32_t)st * S::kRowBytes;
+        const uint32_t run = is_a ? wave * S::kLoadsA + j : S::TM / S::kRunRows + wave * S::kLoadsW + (j - S::kLoadsA);
+        buffer_to_lds(is_a ? buf_a : buf_w, off[j], k_off, lds0 + ring * S::kStageBytes + run * 1024);
     };
 
-    // Operand reads: wave (wm, wn) covers A rows 64 wm .. +63 and W rows
-    // 64 wn .. +63; lane l reads row 16 i + l%16 of its quarter, piece
-    // 4 ks + l/16 (k-step ks of 32), at slot piece ^ (l & 7).
+    // Operands: lane l reads row 16 i + l % 16 of its wave's rows, piece
+    // 4 ks + l / 16 of k-step ks (the slots repeat every 16 rows).
     const int wm = wave & 1, wn = wave >> 1;
-    const uint32_t row_l = (uint32_t)(lane & 15);
-    uint32_t op_off[2];
+    uint32_t op[S::KS];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) op_off[ks] = row_l * 128 + ((((uint32_t)(4 * ks + (lane >> 4))) ^ (lane & 7)) << 4);
+    for (int ks = 0; ks < S::KS; ++ks)
+        op[ks] = (lane & 15) * S::kRowBytes + 16 * S::slot(lane & 15, 4 * ks + (lane >> 4));
+    // W's operands meet every group of a stage's products and are
+    // double-buffered; A's meet one group each, and the next stage's replace
+    // them in place right after it.
+    struct FragsW {
+        bf16x8 w[S::KS][S::NI];
+    };
+    bf16x8 fa[S::KS][S::MI];
+    auto read_a = [&](int ring, int ks, int i) {
+        fa[ks][i] = as_bf16x8(*reinterpret_cast<const u32x4*>(
+            smem + ring * S::kStageBytes + op[ks] + (wm * S::TM / 2 + 16 * i) * S::kRowBytes));
+    };
+    auto read_w = [&](FragsW& f, int ring, int ks, int i) {
+        f.w[ks][i] = as_bf16x8(*reinterpret_cast<const u32x4*>(
+            smem + ring * S::kStageBytes + op[ks] + (S::TM + wn * S::TN / 2 + 16 * i) * S::kRowBytes));
+    };
 
-    f32x4 acc[4][4];
+    f32x4 acc[S::NI][S::MI];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < S::NI; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < S::MI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    load_tiles(0, 0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    for (int kt = 0; kt < KT; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < KT) load_tiles(kt + 1, buf ^ 1);
-        const char* A = sa[buf] + wm * 64 * 128;
-        const char* Wt = sw[buf] + wn * 64 * 128;
+    // Stage st: its operands are in `cur` (read from LDS during stage st - 1)
+    // and its ring slot is free once every wave has passed the barrier, so
+    // stage st + STAGES is copied there; stage st + 1, which has landed by
+    // then, is read into `nxt`; both are spread between the products.
+    auto stage = [&](int st, int ring, FragsW& cur, FragsW& nxt, auto steady) {
+        constexpr bool STEADY = decltype(steady)::value;  // more stages to copy: no branches
+        if (STEADY || st + S::STAGES - 1 < n_st)
+            wait_loads<(S::STAGES - 2) * S::kLoads>();
+        else
+            wait_loads<0>();
+        barrier();
+        const bool more = STEADY || st + S::STAGES < n_st, next = STEADY || st + 1 < n_st;
+        const int ring1 = ring + 1 == S::STAGES ? 0 : ring + 1;
+        constexpr int kGroups = S::KS * S::MI;               // groups of NI products
+        constexpr int kReadsW = S::KS * S::NI;
+        // one copy or read at a time between two products, so that its issue
+        // hides behind the product before it
+        constexpr int kProducts = kGroups * S::NI;
+        // a ring of two waits for these copies at the stage's end: early
+        constexpr int kCopyProducts = S::STAGES == 2 ? kProducts * 5 / 8 : kProducts;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 wf[4], af[4];
+        for (int gi = 0; gi < kGroups; ++gi) {
+            const int ks = gi / S::MI, j = gi % S::MI;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                wf[i] = as_bf16x8(*reinterpret_cast<const u32x4*>(Wt + op_off[ks] + i * 16 * 128));
-                af[i] = as_bf16x8(*reinterpret_cast<const u32x4*>(A + op_off[ks] + i * 16 * 128));
+            for (int i = 0; i < S::NI; ++i) {
+                const int u = gi * S::NI + i;
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_into(acc[i][j], cur.w[ks][i], fa[ks][j]);
+                if (more) {
+#pragma unroll
+                    for (int l = u * S::kLoads / kCopyProducts; l < (u + 1) * S::kLoads / kCopyProducts; ++l)
+                        if (l < S::kLoads) load(st + S::STAGES, ring, l);
+                }
+                if (next) {
+#pragma unroll
+                    for (int l = u * kReadsW / kProducts; l < (u + 1) * kReadsW / kProducts; ++l)
+                        read_w(nxt, ring1, l / S::NI, l % S::NI);
+                    if (i == S::NI / 2 && gi > 0) read_a(ring1, (gi - 1) / S::MI, (gi - 1) % S::MI);
+                }
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = mfma16x16x32(wf[i], af[j], acc[i][j]);
         }
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of the next tiles have landed
-        __syncthreads();                // ... and every wave is done with this buffer
+        __builtin_amdgcn_sched_barrier(0);
+        if (next) read_a(ring1, S::KS - 1, S::MI - 1);
+    };
+
+#pragma unroll
+    for (int st = 0; st < S::STAGES; ++st)
+        if (st < n_st) {
+#pragma unroll
+            for (int l = 0; l < S::kLoads; ++l) load(st, st, l);
+        }
+    if (n_st >= S::STAGES)
+        wait_loads<(S::STAGES - 1) * S::kLoads>();
+    else
+        wait_loads<0>();
+    barrier();
+    FragsW f0, f1;
+#pragma unroll
+    for (int ks = 0; ks < S::KS; ++ks) {
+#pragma unroll
+        for (int i = 0; i < S::NI; ++i) read_w(f0, 0, ks, i);
+#pragma unroll
+        for (int i = 0; i < S::MI; ++i) read_a(0, ks, i);
+    }
+    int ring = 0, st = 0;
+    for (; st + 1 + S::STAGES < n_st; st += 2) {
+        stage(st, ring, f0, f1, std::true_type{});
+        ring = ring + 1 == S::STAGES ? 0 : ring + 1;
+        stage(st + 1, ring, f1, f0, std::true_type{});
+        ring = ring + 1 == S::STAGES ? 0 : ring + 1;
+    }
+    for (; st < n_st; st += 2) {
+        stage(st, ring, f0, f1, std::false_type{});
+        ring = ring + 1 == S::STAGES ? 0 : ring + 1;
+        if (st + 1 < n_st) stage(st + 1, ring, f1, f0, std::false_type{});
+        ring = ring + 1 == S::STAGES ? 0 : ring + 1;
     }
 
-    // Epilogue: acc[i][j] holds C[m][n .. n+3] with m = m0 + 64 wm + 16 j +
-    // l%16 and n = n0 + 64 wn + 16 i + 4 (l/16).
+    // the last products' results, before anything reads them (the compiler
+    // does not count the products' latency in inline assembly)
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+
+    // Epilogue: acc[i][j] holds C[m][n .. n+3] with m = m0 + TM/2 wm + 16 j +
+    // l%16 and n = n0 + TN/2 wn + 16 i + 4 (l/16).
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int64_t m = m0 + 64 * wm + 16 * j + (lane & 15);
+    for (int j = 0; j < S::MI; ++j) {
+        const int64_t m = m0 + S::TM / 2 * wm + 16 * j + (lane & 15);
         if (m >= g.M) continue;
+        f32x4 r[S::NI];
+        if constexpr (OUT == kOutResid) {  // a row's residual values, their loads in flight together
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int n = n0 + 64 * wn + 16 * i + 4 * (lane >> 4);
+            for (int i = 0; i < S::NI; ++i)
+                r[i] = g.resid ? *reinterpret_cast<const f32x4*>(g.resid + m * g.N + n0 + S::TN / 2 * wn + 16 * i + 4 * (lane >> 4))
+                               : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        int64_t head_row = 0;
+        if constexpr (OUT == kOutHeads) head_row = m / g.L * g.H * g.L + m % g.L;
+#pragma unroll
+        for (int i = 0; i < S::NI; ++i) {
+            const int n = n0 + S::TN / 2 * wn + 16 * i + 4 * (lane >> 4);
             f32x4 c = acc[i][j];
-            if (g.bias) {
-                const f32x4 bv = *reinterpret_cast<const f32x4*>(g.bias + n);
-                c += bv;
-            }
+            if (g.bias) c += *reinterpret_cast<const f32x4*>(g.bias + n);
             if constexpr (OUT == kOutResid) {
-                f32x4 r = g.resid ? *reinterpret_cast<const f32x4*>(g.resid + m * g.N + n) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) r[e] = fmaf(g.sign, c[e], r[e]);
-                *reinterpret_cast<f32x4*>(g.out_f32 + m * g.N + n) = r;
+                for (int e = 0; e < 4; ++e) r[i][e] = fmaf(g.sign, c[e], r[i][e]);
+                *reinterpret_cast<f32x4*>(g.out_f32 + m * g.N + n) = r[i];
             } else if constexpr (OUT == kOutReluBf16) {
                 const uint2 p = make_uint2(pack_bf16x2(fmaxf(c[0], 0.f), fmaxf(c[1], 0.f)),
                                            pack_bf16x2(fmaxf(c[2], 0.f), fmaxf(c[3], 0.f)));
                 *reinterpret_cast<uint2*>(g.out_bf16 + m * g.N + n) = p;
             } else {
-                const int64_t bb = m / g.L, l = m % g.L;
                 const int h = n >> 6, e = n & 63;
                 const uint2 p = make_uint2(pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3]));
-                *reinterpret_cast<uint2*>(g.out_bf16 + ((bb * g.H + h) * g.L + l) * 64 + e) = p;
+                *reinterpret_cast<uint2*>(g.out_bf16 + (head_row + (int64_t)h * g.L) * 64 + e) = p;
             }
         }
     }
 }
 
+template <class S, int IN, int OUT>
+hipError_t launch_shape(const GemmArgs& g, hipStream_t stream) {
+    const int64_t tiles = (int64_t)(g.N / S::TN) * ((g.M + S::TM - 1) / S::TM);
+    auto* k = &gemm_bf16_kernel<S, IN, OUT>;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::kLds);
+    k<<<(unsigned)tiles, 256, S::kLds, stream>>>(g);
+    return hipGetLastError();
+}
+
 template <int IN, int OUT>
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream) {
-    const int64_t tiles = (int64_t)(g.N / kTile) * ((g.M + kTile - 1) / kTile);
-    if (tiles == 0) return hipSuccess;
-    gemm_bf16_kernel<IN, OUT><<<(unsigned)tiles, kGemmThreads, 0, stream>>>(g);
-    return hipGetLastError();
+    if (g.M == 0) return hipSuccess;
+    // Tiles of 256 x 256 (one workgroup a CU) where they fill whole waves of
+    // the chip's 256 CUs to three quarters: at 16384 x 1024 x 4096 (256 tiles)
+    // 128 us against 143 with tiles of 128 and 209 with 64; at 3000 x 4096 x
+    // 1024 (192 tiles) 41 against 37.  Tiles of 128 from one per CU on: 15.3 us
+    // against 22.4 with 64 at 4095 x 2048 x 512 (512 tiles); below that the
+    // smaller tiles spread the work further: 17.1 against 28 at 4095 x 512 x
+    // 2048 (128 tiles), 42 against 48 at 3000 x 1024 x 4096 (192).
+    auto tiles = [&](int t) { return g.N % t ? 0 : (int64_t)(g.N / t) * ((g.M + t - 1) / t); };
+    const int64_t t256 = tiles(256), waves = (t256 + 255) / 256;
+    if (t256 > 0 && 4 * t256 >= 3 * 256 * waves) return launch_shape<GemmShape<256, 256, 64, 2>, IN, OUT>(g, stream);
+    if (tiles(128) >= 256) return launch_shape<GemmShape<128, 128, 64, 2>, IN, OUT>(g, stream);
+    return launch_shape<GemmShape<64, 64, 64, 4>, IN, OUT>(g, stream);
 }
 
 }  // namespace
