@@ -56,6 +56,8 @@
 #include "attn_common.h"
 #include "launch.h"
 
+#include <type_traits>
+
 namespace lsh {
 namespace {
 
@@ -456,22 +458,259 @@ __global__ __launch_bounds__((FwdGeom<M, AFTER>::kThreads), (FwdGeom<M, AFTER>::
     flush();
 }
 
-// fp32 path: one workgroup per chunk of M sorted slots (M = 64, or 128, the
-// chunk length of the paper's usual configuration), one lane per query in
-// each of KS waves, exact fp32 arithmetic on the VALU with an online softmax
-// over the query's keys.  Wave s takes every KS-th key of the query's range;
-// the KS partial softmaxes (max, sum, weighted row) are merged at the end.  The window is chunks c-1 .. c+after; it is walked one chunk at a
-// time (the query's own chunk first), each staged in LDS.  Two variants the
-// paper does not spell out: a look-ahead of `after` chunks, and attending
-// across buckets (every key of the window is a target, and N_ij counts the
-// rounds in which j falls in i's window, from undo).
-template <int M, int KS>
-__global__ __launch_bounds__(M * KS) void attn_fwd_f32_kernel(
+// fp32 path.  One workgroup per chunk of M sorted slots (64 or 128), 16
+// queries per wave.  The window (chunks c-1 .. c+after) passes through LDS in
+// pieces of 64 slots, two of them in flight, gathered through perm straight
+// from global memory.  Products run on the fp32 matrix cores
+// (v_mfma_f32_16x16x4_f32: fp32 operands and sums), in the layout of the bf16
+// kernel: S^T = K Q^T per 16-key tile, so that a lane holds four keys of one
+// query, the online softmax on those, and the four weights are the B operand
+// of O^T += V^T P^T as they are.  k-step s of lane group g is dim 16 g + s of
+// S and key 4 g + s of P V.  Exponentials and logarithms are the library's
+// expf and logf in natural units; logits, weights and sums are fp32.
+// Bound by latency for small calls (two gathers and a barrier each) and by the
+// matrix cores for large ones (1024 cycles per tile of 16 x 16).  Against the
+// earlier kernel (a lane per query, every key row broadcast from LDS to 64
+// dependent FMAs): L = 1K, one head 44 -> 15 us; 2 x 4 x 6001, 4 rounds
+// 499 -> 108 us; errors against 64 bits unchanged (1e-7).
+constexpr int kPiece = 64;  // slots of a staged piece
+
+// LDS slots of the sixteen 16-byte pieces of an fp32 row.  K rows are read as
+// pieces 4 g + i of row n by lane (n, g): the rows and pieces of the sixteen
+// lanes that the LDS serves together (lanes 0-3, 12-15, 20-23 and 24-27, and
+// their complement) then fall into sixteen different slots.  V rows are read
+// four bytes at a time, rows 4 g + j: the lane groups' pieces differ in their
+// upper bits.
+__device__ __forceinline__ int kslot(int row, int piece) {
+    return piece ^ (((row >> 3) & 1) * 12 + (row & 3));
+}
+__device__ __forceinline__ int vslot(int row, int piece) { return piece ^ (((row >> 2) & 3) * 4); }
+
+template <int NW>
+struct F32Shared {
+    float Ks[2][kPiece * kHeadDim];
+    float Vs[2][kPiece * kHeadDim];
+    uint32_t sig[2][kPiece][NW > 0 ? NW : 1];  // bucket signature words of the piece's tokens
+    float inv[kPiece];                         // 1/|k| (0 for a zero row)
+    float tab[kMaskedIndex + 1];               // log N by mismatch count
+    int odd[2];                                // nonzero: the piece's V rows are not all finite
+};
+
+template <int NW, int M>
+__global__ __launch_bounds__(M * 4) void attn_fwd_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ v, const int32_t* __restrict__ buckets,
-    const int32_t* __restrict__ perm, const int32_t* __restrict__ undo,
-    const int32_t* __restrict__ bstart, float* __restrict__ o_rounds,
-    float* __restrict__ lse_rounds, int L, int n_r, int n_b, int causal, int after, int across,
-    float scale, float self_mask) {
+    const int32_t* __restrict__ perm, const int32_t* __restrict__ bstart, float* __restrict__ o_rounds,
+    float* __restrict__ lse_rounds, int L, int n_r, int n_b, int causal, int after, float scale, float self_mask) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    F32Shared<NW>& S = *reinterpret_cast<F32Shared<NW>*>(smem);
+    constexpr int kWaves = M / 16;
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t seg = blockIdx.y;
+    const int64_t bh = seg / n_r;
+    const int r = (int)(seg % n_r);
+    const int c = blockIdx.x;
+    const int32_t* pseg = perm + seg * L;
+    const float* qh = q + bh * L * kHeadDim;
+    const float* vh = v + bh * L * kHeadDim;
+    if (tid <= kMaskedIndex) S.tab[tid] = logf((float)max(n_r - tid, 1));
+
+    const int w_lo = max(0, (c - 1) * M), w_hi = min(L, (c + 1 + after) * M) - 1;  // window slots
+    const int n_pieces = (w_hi - w_lo) / kPiece + 1;
+    auto piece_pos = [&](int p) -> int {  // position of slot `lane` of piece p (past the window: any valid one)
+        return min(max(pseg[min(w_lo + p * kPiece + lane, L - 1)], 0), L - 1);
+    };
+    // Gather piece p: wave w copies K and V rows (64 / kWaves) w .., four rows
+    // per instruction; the first wave also packs the tokens' ids.
+    auto stage = [&](int p, int pos) {
+        const int b = p & 1;
+#pragma unroll
+        for (int k = 0; k < kPiece / kWaves / 4; ++k) {
+            const int r0 = wave * (kPiece / kWaves) + 4 * k, row = r0 + g;
+            const int64_t src = (int64_t)__shfl(pos, row) * kHeadDim;
+            copy16_to_lds(qh + src + 4 * kslot(row, n), &S.Ks[b][r0 * kHeadDim]);
+            copy16_to_lds(vh + src + 4 * vslot(row, n), &S.Vs[b][r0 * kHeadDim]);
+        }
+        if constexpr (NW > 0) {
+            if (wave == kWaves - 1) {
+                const int32_t* row = buckets + (bh * L + pos) * n_r;
+                uint32_t id[2 * NW];
+#pragma unroll
+                for (int k = 0; k < 2 * NW; ++k) id[k] = (uint32_t)row[min(k, n_r - 1)] & 0x3FFu;
+#pragma unroll
+                for (int w = 0; w < NW; ++w)
+                    S.sig[b][lane][w] = (2 * w < n_r ? id[2 * w] << w : 0u) |
+                                        (2 * w + 1 < n_r ? id[2 * w + 1] << (w + 11) : 0u);
+            }
+        }
+    };
+    const int pos0 = piece_pos(0), pos1 = piece_pos(1);
+
+    // this lane's query
+    const int s_q = c * M + 16 * wave + n;
+    const bool has_q = s_q < L;  // a slot past L (a partial last chunk) has no query
+    const int i_q = min(max(pseg[min(s_q, L - 1)], 0), L - 1);
+    stage(0, pos0);
+    if (n_pieces > 1) stage(1, pos1);
+    f32x4 qv[4];  // dims 16 g ..
+#pragma unroll
+    for (int k = 0; k < 4; ++k) qv[k] = reinterpret_cast<const f32x4*>(qh + (int64_t)i_q * kHeadDim + 16 * g)[k];
+    const int32_t* bi = buckets + (bh * L + i_q) * n_r;
+    const int beta = min(max(bi[r], 0), n_b - 1);
+    const int32_t* bs = bstart + seg * (n_b + 1);
+    uint32_t qsig[NW > 0 ? NW : 1];
+    if constexpr (NW > 0) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const uint32_t id0 = (uint32_t)bi[min(2 * w, n_r - 1)] & 0x3FFu;
+            const uint32_t id1 = (uint32_t)bi[min(2 * w + 1, n_r - 1)] & 0x3FFu;
+            qsig[w] = (2 * w < n_r ? id0 << w : 0u) | (2 * w + 1 < n_r ? id1 << (w + 11) : 0u);
+        }
+    }
+    // the query's keys: its bucket's slots inside the window, none later than
+    // itself under causal masking (inside a bucket slot order is position order)
+    const int lo = has_q ? max(bs[beta], w_lo) : 1;
+    const int hi = has_q ? (causal ? s_q - 1 : min(bs[beta + 1] - 1, w_hi)) : 0;
+
+    float m = -__builtin_inff(), l = 0.f;
+    f32x4 o[4] = {};  // O^T: dim 16 db + 4 g + j of query n
+    for (int p = 0; p < n_pieces; ++p) {
+        const int b = p & 1, slot0 = w_lo + p * kPiece;
+        const int pos_next = p + 2 < n_pieces ? piece_pos(p + 2) : 0;
+        if (tid == 0) S.odd[b] = 0;
+        __builtin_amdgcn_s_waitcnt(0);  // this wave's copies have landed
+        __syncthreads();
+        if (tid < 4 * kPiece) {  // four lanes per key: its norm, and whether its V row is finite
+            const int row = tid >> 2, part = tid & 3;
+            float ss = 0.f;
+            uint32_t top = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(&S.Ks[b][row * kHeadDim + 4 * kslot(row, 4 * part + k)]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ss = fmaf(x[e], x[e], ss);
+                const f32x4 y = *reinterpret_cast<const f32x4*>(&S.Vs[b][row * kHeadDim + 16 * part + 4 * k]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) top = max(top, __float_as_uint(y[e]) & 0x7FFFFFFFu);
+            }
+            if (top >= 0x7F800000u) S.odd[b] = 1;
+            ss += dpp_f32<kDppXor1>(ss);
+            ss += dpp_f32<kDppXor2>(ss);
+            if (part == 0) S.inv[row] = ss > 0.f ? 1.f / sqrtf(ss) : 0.f;
+        }
+        __syncthreads();
+        const bool odd = S.odd[b] != 0;  // uniform over the workgroup
+#pragma unroll 1
+        for (int kt = 0; kt < kPiece / 16; ++kt) {
+            const int t0 = slot0 + 16 * kt;
+            if (__ballot(lo <= hi && lo <= t0 + 15 && hi >= t0) == 0) continue;  // no key of any query
+            // four chains of products, added pairwise
+            const int krow = 16 * kt + n;
+            f32x4 ac[4] = {};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(&S.Ks[b][krow * kHeadDim + 4 * kslot(krow, 4 * g + k)]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ac[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], qv[k][e], ac[e], 0, 0, 0);
+            }
+            const int row0 = 16 * kt + 4 * g;  // this lane's four keys
+            const f32x4 ik = *reinterpret_cast<const f32x4*>(&S.inv[row0]);
+            float a[4], mt = -__builtin_inff();
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int t = t0 + 4 * g + j;
+                float logn = 0.f;
+                if constexpr (NW > 0) {
+                    uint32_t diff = 0;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w)
+                        diff = and_or((qsig[w] ^ S.sig[b][row0 + j][w]) + sig_add(w), sig_guard(w), diff);
+                    logn = S.tab[__popc(diff)];
+                }
+                const bool ok = t >= lo && t <= hi && t != s_q;
+                a[j] = ok ? scale * (((ac[0][j] + ac[1][j]) + (ac[2][j] + ac[3][j])) * ik[j]) - logn : -__builtin_inff();
+                mt = fmaxf(mt, a[j]);
+            }
+            mt = max_xor32(max_xor16(mt));  // over the four lane groups of the query
+            const float mn = fmaxf(m, mt);
+            const float off = mn > -__builtin_inff() ? mn : 0.f;
+            const float corr = expf(m - off);
+            f32x4 pw;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pw[j] = expf(a[j] - off);
+            l = l * corr + ((pw[0] + pw[1]) + (pw[2] + pw[3]));
+            m = mn;
+            // the tile's sixteen keys are summed by themselves, then added to
+            // the row: shorter sums, less rounding
+            f32x4 po[4] = {};
+            if (!odd) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int row = row0 + j;
+#pragma unroll
+                    for (int db = 0; db < 4; ++db)
+                        po[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            S.Vs[b][row * kHeadDim + 4 * vslot(row, 4 * db + (n >> 2)) + (n & 3)], pw[j], po[db], 0, 0, 0);
+                }
+            } else {
+                // an infinity or NaN among the values: a masked key's must
+                // not meet a query (0 times it is NaN), so key by key
+#pragma unroll 1
+                for (int key = 0; key < 16; ++key) {
+                    const int row = 16 * kt + key, t = t0 + key;
+                    const float pj = key & 2 ? (key & 1 ? pw[3] : pw[2]) : (key & 1 ? pw[1] : pw[0]);
+                    const float pk = __shfl(pj, 16 * (key >> 2) + n);
+                    if (t < lo || t > hi || t == s_q) continue;
+#pragma unroll
+                    for (int db = 0; db < 4; ++db) {
+                        const f32x4 vv =
+                            *reinterpret_cast<const f32x4*>(&S.Vs[b][row * kHeadDim + 4 * vslot(row, 4 * db + g)]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) po[db][e] = fmaf(pk, vv[e], po[db][e]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[db][e] = fmaf(o[db][e], corr, po[db][e]);
+        }
+        if (p + 2 < n_pieces) {
+            __syncthreads();  // every wave is done with this piece
+            stage(p + 2, pos_next);
+        }
+    }
+    l = sum_xor32(sum_xor16(l));  // each lane group summed its own keys
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss = fmaf(qv[k][e], qv[k][e], ss);
+    ss = sum_xor32(sum_xor16(ss));
+    if (!has_q) return;
+    float* orow = o_rounds + (seg * L + s_q) * kHeadDim + 4 * g;
+    const bool alone = !(l > 0.f);  // only itself left as a target: v_i, log-partition scale*|q_i| - self_mask
+    const float il = alone ? 0.f : 1.f / l;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+        *reinterpret_cast<f32x4*>(orow + 16 * db) =
+            alone ? *reinterpret_cast<const f32x4*>(vh + (int64_t)i_q * kHeadDim + 16 * db + 4 * g) : o[db] * il;
+    if (g == 0) lse_rounds[seg * L + s_q] = alone ? scale * sqrtf(ss) - self_mask : m + logf(l);
+}
+
+// fp32 attention across buckets (every key of the window is a target, N_ij
+// counts the rounds in which j falls in i's window, from undo, and the causal
+// test is on positions): a variant the paper does not spell out.  One workgroup
+// per chunk of M sorted slots, one lane per query in each of KS waves, an
+// online softmax over the query's keys on the VALU.  Wave s takes every KS-th
+// key; the KS partial softmaxes (max, sum, weighted row) are merged at the
+// end.  The window is walked one chunk at a time (the query's own chunk
+// first), each staged in LDS.
+template <int M, int KS>
+__global__ __launch_bounds__(M * KS) void attn_fwd_f32_across_kernel(
+    const float* __restrict__ q, const float* __restrict__ v, const int32_t* __restrict__ perm,
+    const int32_t* __restrict__ undo, float* __restrict__ o_rounds, float* __restrict__ lse_rounds, int L, int n_r,
+    int causal, int after, float scale, float self_mask) {
     // rows padded to 68 floats: 16-byte aligned for the broadcast reads of
     // the key loop
     constexpr int kRow = kHeadDim + 4;
@@ -495,21 +734,9 @@ __global__ __launch_bounds__(M * KS) void attn_fwd_f32_kernel(
     const bool has_q = s_q < L;  // a slot past L (a partial last chunk) has no query
     const int32_t* pseg = perm + seg * L;
     const int i_q = pseg[min(s_q, L - 1)];
-    const int32_t* bi = buckets + (bh * L + i_q) * n_r;
-    const int beta = min(max(bi[r], 0), n_b - 1);
-    const int32_t* bs = bstart + seg * (n_b + 1);
-    const int w_lo = max(0, (c - 1) * M), w_hi = min(L, (c + 1 + after) * M) - 1;  // window slots
-    // the query's keys: its bucket's slots inside the window, or the whole
-    // window across buckets.  No key later than the query under causal
-    // masking: inside one bucket slot order is position order, so that is
-    // the slot bound s_q - 1; across buckets it is a test of positions.
-    const int lo = across ? w_lo : max(bs[beta], w_lo);
-    const int hi = across ? w_hi : (causal ? s_q - 1 : min(bs[beta + 1] - 1, w_hi));
-    const bool pos_causal = across && causal;
-    // across buckets: the query's chunk in every round
-    int ci[16];
-    if (across)
-        for (int rr = 0; rr < n_r; ++rr) ci[rr] = undo[(bh * n_r + rr) * L + i_q] / M;
+    const int lo = max(0, (c - 1) * M), hi = min(L, (c + 1 + after) * M) - 1;  // window slots
+    int ci[16];  // the query's chunk in every round
+    for (int rr = 0; rr < n_r; ++rr) ci[rr] = undo[(bh * n_r + rr) * L + i_q] / M;
 
     float qi[kHeadDim];
     float m = -__builtin_inff(), l = 0.f;
@@ -554,7 +781,7 @@ __global__ __launch_bounds__(M * KS) void attn_fwd_f32_kernel(
         for (int tk = t_lo + ks; tk <= t_hi; tk += KS) {
             if (tk == s_q) continue;
             const int rho = tk - slot0;
-            if (pos_causal && spos[rho] > i_q) continue;
+            if (causal && spos[rho] > i_q) continue;
             // four independent chains: one wave per chunk leaves nothing
             // else to hide a 64-long chain of dependent FMAs
             const f32x4* kr = reinterpret_cast<const f32x4*>(&Ks[rho][0]);
@@ -569,14 +796,9 @@ __global__ __launch_bounds__(M * KS) void attn_fwd_f32_kernel(
             float a = scale * (dot * inv[rho]);
             if (n_r > 1) {
                 int nn = 0;
-                if (across) {
-                    for (int rr = 0; rr < n_r; ++rr) {
-                        const int cj = undo[(bh * n_r + rr) * L + spos[rho]] / M;
-                        nn += cj >= ci[rr] - 1 && cj <= ci[rr] + after;
-                    }
-                } else {
-                    const int32_t* bj = buckets + (bh * L + spos[rho]) * n_r;
-                    for (int rr = 0; rr < n_r; ++rr) nn += bi[rr] == bj[rr];
+                for (int rr = 0; rr < n_r; ++rr) {
+                    const int cj = undo[(bh * n_r + rr) * L + spos[rho]] / M;
+                    nn += cj >= ci[rr] - 1 && cj <= ci[rr] + after;
                 }
                 a -= logf((float)nn);
             }
@@ -749,16 +971,37 @@ hipError_t launch_attn_fwd(int64_t BH, int L, int n_rounds, int n_buckets, int c
     const unsigned segs = (unsigned)(BH * n_rounds);
     if (f32) {
         const dim3 grid((unsigned)((L + chunk - 1) / chunk), segs);
-        if (chunk == 128)
-            attn_fwd_f32_kernel<128, 2><<<grid, 256, 0, stream>>>(
-                static_cast<const float*>(q), static_cast<const float*>(v), buckets, perm, undo,
-                bucket_start, static_cast<float*>(o_rounds), lse_rounds, L, n_rounds, n_buckets,
-                causal ? 1 : 0, after, across ? 1 : 0, scale, self_mask);
-        else
-            attn_fwd_f32_kernel<64, 4><<<grid, 256, 0, stream>>>(
-                static_cast<const float*>(q), static_cast<const float*>(v), buckets, perm, undo,
-                bucket_start, static_cast<float*>(o_rounds), lse_rounds, L, n_rounds, n_buckets,
-                causal ? 1 : 0, after, across ? 1 : 0, scale, self_mask);
+        const float *qf = static_cast<const float*>(q), *vf = static_cast<const float*>(v);
+        float* of = static_cast<float*>(o_rounds);
+        if (across) {
+            if (chunk == 128)
+                attn_fwd_f32_across_kernel<128, 2><<<grid, 256, 0, stream>>>(
+                    qf, vf, perm, undo, of, lse_rounds, L, n_rounds, causal ? 1 : 0, after, scale, self_mask);
+            else
+                attn_fwd_f32_across_kernel<64, 4><<<grid, 256, 0, stream>>>(
+                    qf, vf, perm, undo, of, lse_rounds, L, n_rounds, causal ? 1 : 0, after, scale, self_mask);
+            return hipGetLastError();
+        }
+        auto go = [&](auto nw_tag) {
+            constexpr int NW = decltype(nw_tag)::value;
+            auto launch = [&](auto kernel) {
+                constexpr size_t lds = sizeof(F32Shared<NW>);
+                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                kernel<<<grid, 4 * chunk, lds, stream>>>(qf, vf, buckets, perm, bucket_start, of, lse_rounds, L,
+                                                         n_rounds, n_buckets, causal ? 1 : 0, after, scale, self_mask);
+            };
+            if (chunk == 128)
+                launch(&attn_fwd_f32_kernel<NW, 128>);
+            else
+                launch(&attn_fwd_f32_kernel<NW, 64>);
+        };
+        // signature words: two rounds each, rounded up to a power of two
+        if (n_rounds == 1) go(std::integral_constant<int, 0>{});
+        else if (n_rounds == 2) go(std::integral_constant<int, 1>{});
+        else if (n_rounds <= 4) go(std::integral_constant<int, 2>{});
+        else if (n_rounds <= 8) go(std::integral_constant<int, 4>{});
+        else go(std::integral_constant<int, 8>{});
         return hipGetLastError();
     }
     const uint16_t* qb = static_cast<const uint16_t*>(q);
