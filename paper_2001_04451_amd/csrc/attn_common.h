@@ -76,6 +76,13 @@ __device__ __forceinline__ f32x4 mfma16x16x16(bf16x4 a, bf16x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
+// Two four-element operands as one of eight: a lane's k-slots of two 16-deep
+// products side by side make those of one 16x16x32 product, which takes the
+// matrix cores as long as a 16x16x16 one.
+__device__ __forceinline__ bf16x8 cat4(bf16x4 a, bf16x4 b) {
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // Copy 16 (4) bytes per lane from global memory to LDS at lds_base + 16
 // (4) * lane; lds_base is uniform over the wave.  Written as inline assembly
 // so that the compiler does not order every later LDS read of the step
