@@ -83,6 +83,38 @@ __device__ __forceinline__ bf16x8 cat4(bf16x4 a, bf16x4 b) {
     return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// Work item of a workgroup under a grid of xcd_grid() workgroups: `items` of
+// each of BH (batch, head) slices, a slice's items next to each other.
+// Workgroups go to the XCDs in turn; `sets` slices are under way at a time,
+// each on kXcds / sets of the XCDs (see xcd_sets).
+constexpr int kXcds = 8;
+struct XcdItem {
+    int64_t slice;  // past the last one where there is no work
+    int item;
+};
+__device__ __forceinline__ XcdItem xcd_item(int items, int sets) {
+    const int xcd = (int)(blockIdx.x % kXcds);
+    const uint32_t k = blockIdx.x / kXcds * (uint32_t)(kXcds / sets) + (uint32_t)(xcd / sets);
+    return {(int64_t)(k / (uint32_t)items) * sets + xcd % sets, (int)(k % (uint32_t)items)};
+}
+inline unsigned xcd_grid(int64_t BH, int64_t items, int sets) {
+    const int per = kXcds / sets;
+    return (unsigned)((BH / sets * items + per - 1) / per * kXcds);
+}
+// Slices under way at a time for a chunk kernel that gathers slice_bytes of rows
+// per slice once a round.  Up to an XCD's L2 (4 MB) each XCD keeps to its own
+// slices, whose rows then stay in its L2 from round to round; with larger ones
+// all XCDs walk one slice, whose rows the Infinity Cache keeps.  Whole calls, one
+// slice at a time against eight (us): 32 slices of 4K 98.8 / 96.3, 16 of 16K
+// 226.8 / 224.6, 64 of 8K 680 / 672; but 16 of 64K (16 MB each) 1787 / 1817.  Four
+// at a time gain as much (1 x 4 x 16K, 8 rounds 160.2 / 159.5), two lose (2 of 8K
+// 69.0 / 69.8).  The backward's strips keep their two-dimensional grid: their
+// 32K call was 0.5% slower with this numbering.
+inline int xcd_sets(int64_t BH, int64_t slice_bytes) {
+    if (slice_bytes > (4 << 20)) return 1;
+    return BH % 8 == 0 ? 8 : (BH % 4 == 0 ? 4 : 1);
+}
+
 // Copy 16 (4) bytes per lane from global memory to LDS at lds_base + 16
 // (4) * lane; lds_base is uniform over the wave.  Written as inline assembly
 // so that the compiler does not order every later LDS read of the step

@@ -132,7 +132,7 @@ __global__ __launch_bounds__((FwdGeom<M, AFTER>::kThreads), (FwdGeom<M, AFTER>::
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ v, const uint32_t* __restrict__ rec,
     const int32_t* __restrict__ perm, uint16_t* __restrict__ o_rounds,
     uint8_t* __restrict__ o_exp, float* __restrict__ lse_rounds, int L, int n_r, float scale,
-    float self_mask, int chunks_per_strip) {
+    float self_mask, int chunks_per_strip, int64_t BH, int sets) {
     using G = FwdGeom<M, AFTER>;
     using Shared = FwdShared<NW, M, AFTER>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -143,11 +143,14 @@ __global__ __launch_bounds__((FwdGeom<M, AFTER>::kThreads), (FwdGeom<M, AFTER>::
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;  // query (and key row) of the lane, key group
-    const int64_t seg = blockIdx.y;
-    const int64_t bh = seg / n_r;
-    const int r = (int)(seg % n_r);
     const int n_chunks = (L + M - 1) / M;  // the last may be partial
-    const int c0 = blockIdx.x * chunks_per_strip;
+    const int strips = (n_chunks + chunks_per_strip - 1) / chunks_per_strip;
+    const XcdItem work = xcd_item(strips * n_r, sets);
+    const int64_t bh = work.slice;
+    if (bh >= BH) return;
+    const int r = work.item / strips;
+    const int64_t seg = bh * n_r + r;
+    const int c0 = (work.item - r * strips) * chunks_per_strip;
     const int c1 = min(n_chunks, c0 + chunks_per_strip);
     const float scale_log2e = scale * kLog2e;
     const int32_t* pseg = perm + seg * L;
@@ -903,7 +906,7 @@ __global__ __launch_bounds__(256) void attn_prep_kernel(const uint16_t* __restri
 
 
 template <int NW, int M, int AFTER>
-void launch_kernel(bool causal, dim3 grid, const uint16_t* q, const uint16_t* v, const uint32_t* rec,
+void launch_kernel(bool causal, int64_t BH, int sets, unsigned grid, const uint16_t* q, const uint16_t* v, const uint32_t* rec,
                    const int32_t* perm, uint16_t* o, uint8_t* o_exp, float* lse, int L, int n_r,
                    float scale, float self_mask, int cps, hipStream_t stream) {
     constexpr int kThreads = FwdGeom<M, AFTER>::kThreads;
@@ -911,7 +914,7 @@ void launch_kernel(bool causal, dim3 grid, const uint16_t* q, const uint16_t* v,
     auto go = [&](auto kernel) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds);
-        kernel<<<grid, kThreads, lds, stream>>>(q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps);
+        kernel<<<grid, kThreads, lds, stream>>>(q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, BH, sets);
     };
     if (causal)
         go(&attn_fwd_bf16_kernel<NW, true, M, AFTER>);
@@ -934,15 +937,16 @@ hipError_t launch_bf16(bool causal, int M, int after, const uint16_t* q, const u
     const int64_t n_chunks = (L + M - 1) / M, segs = BH * n_r;
     const int occ = M == 64 ? (after == 0 ? 3 : 2) : 1;
     const int cps = (int)std::max<int64_t>(1, std::min<int64_t>(16, n_chunks * segs / (1024 * occ)));
-    const dim3 grid((unsigned)((n_chunks + cps - 1) / cps), (unsigned)segs);
+    const int sets = xcd_sets(BH, (int64_t)L * 2 * kHeadDim * sizeof(uint16_t));
+    const unsigned grid = xcd_grid(BH, (n_chunks + cps - 1) / cps * n_r, sets);
     if (M == 64 && after == 0)
-        launch_kernel<NW, 64, 0>(causal, grid, q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, stream);
+        launch_kernel<NW, 64, 0>(causal, BH, sets, grid, q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, stream);
     else if (M == 64)
-        launch_kernel<NW, 64, 1>(causal, grid, q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, stream);
+        launch_kernel<NW, 64, 1>(causal, BH, sets, grid, q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, stream);
     else if (after == 0)
-        launch_kernel<NW, 128, 0>(causal, grid, q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, stream);
+        launch_kernel<NW, 128, 0>(causal, BH, sets, grid, q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, stream);
     else
-        launch_kernel<NW, 128, 1>(causal, grid, q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, stream);
+        launch_kernel<NW, 128, 1>(causal, BH, sets, grid, q, v, rec, perm, o, o_exp, lse, L, n_r, scale, self_mask, cps, stream);
     return hipGetLastError();
 }
 

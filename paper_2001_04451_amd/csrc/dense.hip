@@ -44,7 +44,6 @@ namespace {
 constexpr int kDenseWaves = 4;
 constexpr int kKeyBlock = 64;
 constexpr float kDenseFastBound = 60.f;
-constexpr int kXcds = 8;
 constexpr int kSwz = 1;  // LDS row layout (attn_common.h): 16-row operand reads
 constexpr bf16x8 kOnes8 = {(__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f,
                            (__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f};
