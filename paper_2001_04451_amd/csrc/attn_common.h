@@ -120,17 +120,19 @@ inline int xcd_sets(int64_t BH, int64_t slice_bytes) {
 // so that the compiler does not order every later LDS read of the step
 // behind these copies (it cannot tell the slot being filled from the slots
 // being read); the kernel waits for them itself before each barrier.
+// A scalar write of m0 needs one wait state before a copy to LDS reads it
+// (the compiler keeps to that for its own copies, not inside an asm string).
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
     // the same address in every lane; readfirstlane puts it in a scalar register
     return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p);
 }
 __device__ __forceinline__ void copy16_to_lds(const void* src, const void* lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr(lds_base))
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr(lds_base))
                  : "memory", "m0");
 }
 
 __device__ __forceinline__ void copy4_to_lds(const void* src, const void* lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds_addr(lds_base))
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds_addr(lds_base))
                  : "memory", "m0");
 }
 

@@ -121,7 +121,8 @@ __device__ __forceinline__ u32x4 raw_buffer(const void* p, uint64_t bytes) {
 // lds + 16 * lane.  Inline assembly, so that the compiler neither orders LDS
 // reads behind it nor waits for it: the kernel counts its own loads.
 __device__ __forceinline__ void buffer_to_lds(u32x4 buf, uint32_t v_off, uint32_t s_off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(v_off), "s"(buf), "s"(s_off), "s"(lds)
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(v_off), "s"(buf),
+                 "s"(s_off), "s"(lds)
                  : "memory", "m0");
 }
 
