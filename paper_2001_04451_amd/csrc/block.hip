@@ -342,14 +342,18 @@ __global__ __launch_bounds__(256, (S::kLds > 80 * 1024 ? 1 : 2)) void gemm_bf16_
         ring = ring + 1 == S::STAGES ? 0 : ring + 1;
     }
 
-    // the last products' results, before anything reads them (the compiler
-    // does not count the products' latency in inline assembly)
+    // Wait for the last products' results: the compiler does not count the
+    // products' latency in inline assembly.  The epilogue takes the accumulators
+    // from assembly behind this wait, a row block at a time, so that neither a
+    // read nor a spill of one can come before it.
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 
     // Epilogue: acc[i][j] holds C[m][n .. n+3] with m = m0 + TM/2 wm + 16 j +
     // l%16 and n = n0 + TN/2 wn + 16 i + 4 (l/16).
 #pragma unroll
     for (int j = 0; j < S::MI; ++j) {
+#pragma unroll
+        for (int i = 0; i < S::NI; ++i) asm volatile("" : "+a"(acc[i][j]));
         const int64_t m = m0 + S::TM / 2 * wm + 16 * j + (lane & 15);
         if (m >= g.M) continue;
         f32x4 r[S::NI];

@@ -6,7 +6,9 @@ import pytest
 import torch
 
 from gpu_common import log
+from oracle import block as OB
 from paper_2001_04451_amd import lsh
+from paper_2001_04451_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +34,37 @@ def test_linear_tiles(M, N, K):
     assert (err <= bound + 2.0 ** -23 * (resid.abs() + exact.abs())).all()
     relu = lsh.linear_bf16(a, w, bias=bias, relu_bf16=True)
     assert ((relu.double() - exact.relu()).abs() <= bound + 2.0 ** -8 * exact.abs()).all()
+
+
+# The attention half's products in the [B, H, L, 64] layout, batches ending inside row tiles.  The whole call takes
+# 256 x 256 tiles (M = 16362, N = 1024: 256 of them; M = 65000, N = 256: 254) or 128 x 128 (M = 33330, N = 128: 261),
+# a few batches 128 x 128 (M = 4848, N = 1024; M = 26000, N = 256) or 64 x 64 (M = 3333), one batch 64 x 64.  Every
+# tile adds a value's products in the same order, so the results are the same bits; one batch is held to the oracle.
+@pytest.mark.parametrize("B,H,L,few", [(54, 16, 303, 16), (50, 4, 1300, 20), (30, 2, 1111, 3)])
+def test_head_layout_by_tile(B, H, L, few):
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    w = W.BLOCKS["revblock_bf16_L65536"].scaled(B=B, H=H, L=L, d_ff=128, n_buckets=8, n_rounds=1, ff_chunk=0, exact=True)
+    x = W.make_block_inputs(w)
+    host, dev = {}, {}
+    for k, a in x.items():
+        if k not in ("x1", "x2"):
+            bf = a.dtype == np.uint16
+            host[k] = W.as_f64(a, "bf16") if bf else a.astype(np.float64)
+            t = torch.from_numpy(a.view(np.int16) if bf else a).cuda()
+            dev[k] = t.view(torch.bfloat16) if bf else t
+    x1, x2 = torch.from_numpy(x["x1"]).cuda(), torch.from_numpy(x["x2"]).cuda()
+    wd = lsh.BlockWeights(**dev)
+
+    def call(batches):
+        cfg = lsh.BlockConfig.of(w.scaled(B=batches.stop - batches.start))
+        log("heads", B, H, L, batches)
+        return lsh.rev_attention(cfg, wd, x2[batches].contiguous(), x1[batches].contiguous(), -1.0)
+
+    whole = call(slice(0, B))
+    assert torch.equal(call(slice(1, 1 + few)), whole[1:1 + few])
+    for b in (0, B // 2, B - 1):
+        assert torch.equal(call(slice(b, b + 1)), whole[b:b + 1])
+    want = OB.attention_layer(x["x2"][-1:].astype(np.float64), OB.BlockWeights(**host), H, w.chunk, w.causal, w.ln_eps)
+    err = np.abs(whole[-1:].cpu().numpy() - (x["x1"][-1:] - want))
+    assert err.max() <= 2e-2  # the bf16 attention's bound
