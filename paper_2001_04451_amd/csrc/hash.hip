@@ -328,16 +328,19 @@ __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
 #pragma unroll
             for (int w = 1; w < kRefineWaves; ++w) mx = fmaxf(mx, S.mx[w][e16]);
             // |q| max |R_c| bounds every partial sum: above fp32's range a sum
-            // may overflow, and far below it products lose bits that eps does
-            // not count; such an entry gets no candidates
-            const float size = S.qn[e16] * cn;
+            // may overflow, and far below it products (or q's squares, and with
+            // them |q|) lose bits that eps does not count.  Such an entry gets
+            // no candidates, whatever its projections came to (an infinity is
+            // not below any cut).
+            const float qn = S.qn[e16], size = qn * cn;
             const float eps = (float)(64 * (0x1p-23 + 0x1p-24) * 1.05) * size;
-            const float cut = size > 0x1p-80f && size < 0x1p120f ? fmaxf(mx - 2.f * eps, 0.f) : __builtin_inff();
+            const bool bounded = qn > 0x1p-64f && size > 0x1p-80f && size < 0x1p120f;
+            const float cut = fmaxf(mx - 2.f * eps, 0.f);
             uint32_t mine = 0;  // bit 4 tile + j: a candidate
 #pragma unroll
             for (int tile = 0; tile < kRefineTiles; ++tile)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) mine |= (uint32_t)(p[tile][j] >= cut) << (4 * tile + j);
+                for (int j = 0; j < 4; ++j) mine |= (uint32_t)(bounded && p[tile][j] >= cut) << (4 * tile + j);
             while (mine) {
                 const int jj = __ffs((int)mine) - 1;
                 mine &= mine - 1;

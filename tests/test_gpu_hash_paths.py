@@ -48,6 +48,26 @@ def test_hash_close_columns(gpu, dtype, L, n_buckets, copies, k):
     assert np.array_equal(got, want)
 
 
+# Projections outside fp32's range, or of rows or an R near its lower end, where the last pass's fp32 sums say nothing
+# (a partial sum may overflow to an infinity, or to NaN, in a column that does not hold the largest): every row has a
+# column and its copy one ulp away, so that all rows reach the last pass.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("k_q,k_r", [(64, 60), (64, 61), (66, 62), (100, 26), (-75, 40), (-69, 20), (60, -118)])
+def test_hash_fp32_range(gpu, dtype, k_q, k_r):
+    w = small("causal_bf16_L16384", B=1, H=2, L=300, n_buckets=128, n_rounds=2, dtype=dtype)
+    x = W.make_inputs(w)
+    R = x["R"].copy()
+    R[:, :, 1::2] = R[:, :, ::2]
+    R[:, 5, 1::2] = np.nextafter(R[:, 5, 1::2], np.float32(np.inf))
+    q = np.ldexp(W.as_f64(x["q"], dtype).astype(np.float32), k_q)
+    R = np.ldexp(R, k_r)
+    qin = W.f32_to_bf16_bits(q) if dtype == "bf16" else q
+    want, _ = oracle.lsh_hash(W.as_f64(qin, dtype), R.astype(np.float64))
+    log("hash-range", dtype, k_q, k_r)
+    got = lsh.lsh_hash(lsh.Config.of(w), to_device(qin, dtype), to_device(R, "f32")).cpu().numpy()
+    assert np.array_equal(got, want), f"{(got != want).sum()} of {got.size}"
+
+
 # One R per head: slices that end inside a workgroup's rows (L = 1, 255, 300),
 # one head, and more rounds of R than are hashed together (H n_rounds = 1040).
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
