@@ -82,3 +82,43 @@ def test_hash_per_head_slices(gpu, dtype, B, H, L, n_r, n_buckets):
     cfg = lsh.Config.of(w, r_per_head=True)
     got = lsh.lsh_hash(cfg, to_device(x["q"], dtype), to_device(R, "f32")).cpu().numpy()
     assert np.array_equal(got, want)
+
+
+# Above 40 M projections bf16 calls are screened with R's hi plane, then the open rows listed: whole and partial tiles
+# and stages of R (1, 2, 3, 10 and 16 tiles), one R or one per head (slices that end inside a workgroup's rows, several
+# batches, H n_rounds = 1120: a full and a partial group of heads; 1040: the last head alone, in one pass).  Rows are
+# drawn from a pool whose ids come from the oracle: zero rows, bf16 subnormals, a few large values beside small ones,
+# scales of 2^-60 .. 2^60, rounds of R at 2^-60 and 2^50.  tied: every column has an equal, a negated or a one-ulp copy,
+# so that every row is left open by the screen and by the listed pass (full segments and lists).
+@pytest.mark.parametrize("tied", [False, True])
+@pytest.mark.parametrize("B,H,L,n_r,n_buckets,per_head", [
+    (1, 2, 41001, 16, 2, False), (1, 2, 20501, 16, 66, False), (2, 1, 13701, 16, 192, False),
+    (2, 1, 8201, 8, 640, False), (1, 2, 9001, 5, 1022, False),
+    (1, 2, 41001, 16, 2, True), (3, 5, 2801, 16, 66, True), (2, 3, 9001, 4, 1022, True),
+    (2, 70, 430, 16, 1022, True), (1, 65, 700, 16, 1022, True)])
+def test_hash_screened(gpu, B, H, L, n_r, n_buckets, per_head, tied):
+    half = n_buckets // 2
+    assert B * H * L * n_r * -(-half // 32) * 32 > 40 << 20
+    rng = np.random.default_rng(L + n_buckets)
+    pool, sets = 250, H if per_head else 1
+    R = rng.standard_normal((sets, n_r, 64, half), dtype=np.float32)
+    if tied and half > 1:
+        R[..., 1::3] = R[..., :-1:3][..., :R[..., 1::3].shape[-1]]
+        R[..., 2::3] = -R[..., 1::3][..., :R[..., 2::3].shape[-1]]
+        R[..., 7, 1::6] = np.nextafter(R[..., 7, 1::6], np.float32(np.inf))
+    R[:, 0] *= np.float32(2.0 ** -60)
+    R[:, -1] *= np.float32(2.0 ** 50)
+    q = rng.standard_normal((1, sets, pool, 64)) * np.ldexp(1.0, rng.integers(-60, 61, (1, sets, pool, 1)))
+    q[:, :, 1::8] = 0
+    q[:, :, 2::8] = rng.standard_normal(q[:, :, 2::8].shape) * 2.0 ** -130
+    q[:, :, 3::8, :4] *= 2.0 ** 30
+    bits = W.f32_to_bf16_bits(q.astype(np.float32))
+    want, _ = oracle.lsh_hash(W.as_f64(bits, "bf16"), (R if per_head else R[0]).astype(np.float64))
+    pick = rng.integers(0, pool, (B, H, L))
+    head = np.arange(H)[None, :, None] % sets
+    w = small("causal_bf16_L16384", B=B, H=H, L=L, n_buckets=n_buckets, n_rounds=n_r)
+    log("hash-screened", B, H, L, n_r, n_buckets, per_head, tied)
+    got = lsh.lsh_hash(lsh.Config.of(w, r_per_head=per_head), to_device(bits[0][head, pick], "bf16"),
+                       to_device(R if per_head else R[0], "f32")).cpu().numpy()
+    bad = got != want[0][head, pick]
+    assert not bad.any(), f"{bad.sum()} of {got.size}"

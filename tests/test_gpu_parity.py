@@ -252,8 +252,9 @@ def test_hash_exact_ties(gpu, dtype):
 @pytest.mark.parametrize("n_buckets", [2, 6, 66, 128, 200, 640, 1022])
 def test_hash_bucket_counts(gpu, dtype, n_buckets):
     """Bucket counts the five workloads do not use: rounds of 1 to 511
-    columns, so R's stages hold 1, 2, 4, 8 or 16 tiles and the last tile or
-    stage of a round is partial.  Bit for bit against the oracle."""
+    columns, so R's stages hold 1, 2, 4 or 8 tiles (bf16, both planes: 1 or
+    2; larger bf16 calls are screened first, test_gpu_hash_paths.py) and the
+    last tile or stage of a round is partial.  Bit for bit against the oracle."""
     w = small("causal_bf16_L16384", B=1, H=2, L=1536, n_buckets=n_buckets, n_rounds=2, dtype=dtype)
     x, q64, _ = _inputs(w)
     want, near = oracle.lsh_hash(q64, x["R"].astype(np.float64))
