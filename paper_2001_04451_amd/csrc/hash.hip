@@ -213,11 +213,17 @@ __device__ __forceinline__ float q_value(const void* q, int64_t row, int k) {
 // Measured against the earlier form (lane = entry, R by scalar loads one t
 // after another, 64 entries a block): 32 -> 6.2 us at L = 1K fp32, 23 -> 9.4
 // at 4 x 8 x 4K with 64 buckets, 39 -> 29 at 16 x 64K with 8 rounds of 1024.
+// Long lists are dealt out over all blocks.  With each round's list left to its
+// own 512 / rounds blocks, one round of equal columns took the hash of 16 x 64K
+// (8 rounds) 64 ms against 16 now and 17 in the earlier form (256 blocks a
+// round), and a head of zero rows among 8 of 12K, one R each, 1.54 ms against
+// 0.4 and 1.29; ordinary calls the same in both (0.667 and 0.075 ms).
 constexpr int kRefineThreads = 512;
 constexpr int kRefineWaves = kRefineThreads / 64;
 constexpr int kRefineGroup = 16;     // entries per pass: a matrix tile's columns
 constexpr int kRefineCand = 8;       // candidate lanes per entry
 constexpr int kRefineTiles = 4;      // 16-column tiles per wave in pass 1
+constexpr int kRefineOwn = 2;        // groups of its own round's list that a block takes before other rounds'
 static_assert(kRefineWaves * kRefineTiles * 16 >= 512, "pass 1 covers n_b / 2 <= 512 columns");
 
 __device__ __forceinline__ void better(double v, int i, double& bv, int& bi) {
@@ -241,31 +247,45 @@ __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
     const int* __restrict__ lists, const int* __restrict__ counts, const float* __restrict__ col_norm_max,
     const int* __restrict__ r_exp, int32_t* __restrict__ buckets_) {
     __shared__ __attribute__((aligned(16))) RefineShared S;
-    const int r = blockIdx.y;  // round of the R sets: r % n_r of its rows
-    const int n = counts[r];
+    const int lane = lane_id(), e16 = lane & 15, g16 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c0 = wave * kRefineTiles * 16;  // this wave's columns in pass 1
+    const bool has_cols = c0 < half;          // uniform per wave
+    // A round's own blocks (those of its blockIdx.y) take kRefineOwn groups each
+    // of its list, which is all of an ordinary one; the rest of a long list is
+    // dealt out over the whole grid, so that one round's, or one head's, does
+    // not wait for its own few blocks.  Lane l looks at the round k0 + l places
+    // after the block's own.
+    const int rounds = gridDim.y, own = kRefineOwn * gridDim.x;
+    for (int k0 = 0; k0 < rounds; k0 += 64) {
+    const int k_l = k0 + lane;
+    const int n_l = k_l < rounds ? counts[(blockIdx.y + k_l) % rounds] : 0;
+    uint64_t todo = __ballot((n_l + kRefineGroup - 1) / kRefineGroup >
+                             (k_l == 0 ? 0 : own + k_l * (int)gridDim.x) + (int)blockIdx.x);
+    for (; todo; todo &= todo - 1) {  // uniform per block
+    const int kk = __ffsll((unsigned long long)todo) - 1;
+    const int n = __builtin_amdgcn_readlane(n_l, kk);
     const int groups = (n + kRefineGroup - 1) / kRefineGroup;
-    if ((int)blockIdx.x >= groups) return;  // uniform per block
+    const int r = (blockIdx.y + k0 + kk) % rounds;  // round of the R sets: r % n_r of its rows
     int32_t* buckets = buckets_ + r % n_r;
     const int* list = lists + list_stride * r;
     const float* Rt = r_t + (size_t)r * half_pad * kHeadDim;  // [column][t], zero columns up to half_pad
-    const int lane = lane_id(), e16 = lane & 15, g16 = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // max_c |R_c| of the round as given (the planes' norms are of R * 2^r_exp)
     const float cn = r_exp ? ldexpf(col_norm_max[r], -r_exp[r]) : col_norm_max[r];
-    const int c0 = wave * kRefineTiles * 16;  // this wave's columns in pass 1
-    const bool has_cols = c0 < half;          // uniform per wave
     f32x4 rc[kRefineTiles][4];                // column c0 + 16 tile + e16 (clamped), t = 16 g16 ..
     if (has_cols) {
+        int col = c0 + e16;
+        asm("" : "+v"(col));  // formed here: the addresses, kept over the loops, were spilled
 #pragma unroll
         for (int tile = 0; tile < kRefineTiles; ++tile) {
-            const f32x4* src = reinterpret_cast<const f32x4*>(
-                Rt + (size_t)min(c0 + 16 * tile + e16, half - 1) * kHeadDim + 16 * g16);
+            const uint32_t src = (uint32_t)min(col + 16 * tile, half - 1) * kHeadDim + 16 * g16;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) rc[tile][k] = src[k];
+            for (int k = 0; k < 4; ++k) rc[tile][k] = *reinterpret_cast<const f32x4*>(Rt + src + 4 * k);
         }
     }
 
-    for (int g = blockIdx.x; g < groups; g += gridDim.x) {
+    for (int g = (k0 + kk == 0 ? 0 : own + (k0 + kk) * (int)gridDim.x) + blockIdx.x; g < groups;
+         g += g < own ? gridDim.x : gridDim.x * rounds) {
         if (threadIdx.x < kRefineGroup) S.cnt[threadIdx.x] = 0;
         // pass 1: the waves with columns (wave 0 always has some, and also
         // keeps the q rows for pass 2)
@@ -367,12 +387,12 @@ __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
                 // the sum rounds exactly as the plain loop does.
                 double acc = 0.0;
 #pragma unroll 1
-                for (int u0 = 0; u0 < 16; u0 += 8) {
-                    f32x4 xr[8];
+                for (int u0 = 0; u0 < 16; u0 += 4) {
+                    f32x4 xr[4];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) xr[u] = col[u0 + u];
+                    for (int u = 0; u < 4; ++u) xr[u] = col[u0 + u];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
+                    for (int u = 0; u < 4; ++u) {
                         const f32x4 xq = *reinterpret_cast<const f32x4*>(&S.qs[i][4 * (u0 + u)]);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) acc = __dadd_rn(acc, __dmul_rn((double)xq[e], (double)xr[u][e]));
@@ -419,6 +439,8 @@ __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
             if (lane == 0) buckets[(int64_t)list[ei] * n_r] = bi;
         }
         __syncthreads();  // the group's LDS is reused by the next one
+    }
+    }
     }
 }
 
@@ -1266,8 +1288,7 @@ hipError_t launch_hash_sets(const void* q, bool f32, const Slices& sl, const Sli
     const int64_t n_slices = sl.set_rows / sl.rows * sl.sets;
     const unsigned grid = (unsigned)(n_slices * sl.blocks);
     // Refinement blocks: about two per CU over all rounds.  A typical list holds
-    // 0.1% of the rows (64 groups of 16 at 1M rows); longer lists are strided,
-    // and a block keeps its R for all of its groups.
+    // 0.1% of the rows (64 groups of 16 at 1M rows).
     const unsigned refine_blocks = (unsigned)std::max<int64_t>(
         1, std::min<int64_t>(std::max(1, 512 / rounds), (sl.set_rows + kRefineGroup - 1) / kRefineGroup));
     if (f32) {

@@ -68,6 +68,24 @@ def test_hash_fp32_range(gpu, dtype, k_q, k_r):
     assert np.array_equal(got, want), f"{(got != want).sum()} of {got.size}"
 
 
+# One round (of one head) with columns in equal pairs, so that only its list is long: every block of the last pass
+# takes a share of it, past the 64 rounds that a block looks at together (H n_rounds = 1040 in groups of 1024 and 16).
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H,L,n_r,n_buckets,at", [(1, 2, 9001, 3, 130, (0, 1)), (40, 65, 61, 16, 34, (63, 15)),
+                                                    (40, 65, 61, 16, 34, (64, 3)), (60, 70, 61, 1, 66, (2, 0))])
+def test_hash_one_long_list(gpu, dtype, B, H, L, n_r, n_buckets, at):
+    w = small("causal_bf16_L16384", B=B, H=H, L=L, n_buckets=n_buckets, n_rounds=n_r, dtype=dtype)
+    x = W.make_inputs(w)
+    per_head = H > 2
+    R = np.random.default_rng(9).standard_normal((H if per_head else 1, n_r, 64, n_buckets // 2), dtype=np.float32)
+    R[at][:, 1::2] = R[at][:, :-1:2][:, :R[at][:, 1::2].shape[1]]
+    R = R if per_head else R[0]
+    want, _ = oracle.lsh_hash(W.as_f64(x["q"], dtype), R.astype(np.float64))
+    log("hash-long-list", dtype, B, H, L, n_r, n_buckets, at)
+    got = lsh.lsh_hash(lsh.Config.of(w, r_per_head=per_head), to_device(x["q"], dtype), to_device(R, "f32")).cpu().numpy()
+    assert np.array_equal(got, want)
+
+
 # One R per head: slices that end inside a workgroup's rows (L = 1, 255, 300),
 # one head, and more rounds of R than are hashed together (H n_rounds = 1040).
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
