@@ -36,6 +36,23 @@ def test_linear_tiles(M, N, K):
     assert ((relu.double() - exact.relu()).abs() <= bound + 2.0 ** -8 * exact.abs()).all()
 
 
+# The walk over the tiles (bands of an eighth of the row tiles, four columns at a time, an eighth of the tiles to an XCD)
+# takes every tile once, whatever their counts: fewer than eight tiles, a short last band, a last group of one to three
+# columns.  Row and column counts in tiles of 64 (128 for the last two: 257 and 33 row tiles).
+@pytest.mark.parametrize("M,N", [(1, 128), (150, 128), (400, 384), (577, 128), (1100, 640), (1500, 896), (2113, 384),
+                                 (32800, 128), (4200, 1152)])
+def test_linear_walk(M, N):
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    g = torch.Generator().manual_seed(M + N)
+    a = torch.randint(-4, 5, (M, 64), generator=g).bfloat16().cuda()
+    w = torch.randint(-4, 5, (N, 64), generator=g).bfloat16().cuda()
+    log("linear-walk", M, N)
+    # NaN where a call before this one left its output: a tile that no workgroup takes shows
+    torch.full((M, N), float("nan"), device="cuda")
+    assert torch.equal(lsh.linear_bf16(a, w), a.float() @ w.float().t())  # whole numbers: exact in any order
+
+
 # The attention half's products in the [B, H, L, 64] layout, batches ending inside row tiles.  The whole call takes
 # 256 x 256 tiles (M = 16362, N = 1024: 256 of them; M = 65000, N = 256: 254) or 128 x 128 (M = 33330, N = 128: 261),
 # a few batches 128 x 128 (M = 4848, N = 1024; M = 26000, N = 256) or 64 x 64 (M = 3333), one batch 64 x 64.  Every
