@@ -400,16 +400,27 @@ hipError_t launch_shape(const GemmArgs& g, hipStream_t stream) {
 template <int IN, int OUT>
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream) {
     if (g.M == 0) return hipSuccess;
-    // Tiles of 256 x 256 (one workgroup a CU) where they fill whole waves of
-    // the chip's 256 CUs to three quarters: at 16384 x 1024 x 4096 (256 tiles)
-    // 128 us against 143 with tiles of 128 and 209 with 64; at 3000 x 4096 x
-    // 1024 (192 tiles) 41 against 37.  Tiles of 128 from one per CU on: 15.3 us
-    // against 22.4 with 64 at 4095 x 2048 x 512 (512 tiles); below that the
-    // smaller tiles spread the work further: 17.1 against 28 at 4095 x 512 x
-    // 2048 (128 tiles), 42 against 48 at 3000 x 1024 x 4096 (192).
+    // Tiles of 256 x 256, one workgroup a CU, where they fill whole waves of the
+    // chip's 256 CUs well enough.  Nothing overlaps a workgroup's first copies and
+    // its epilogue, which weigh more the fewer stages there are, so the fill that
+    // it takes falls with K.  us with tiles of 256 / 128 (share of the waves filled):
+    //   K >= 1536: 3/4.  16384 x 1024 x 4096 119 / 132 (1), 12,100 x 1024 x 2048
+    //   59 / 65 (0.75), 8192 x 1536 x 1536 53 / 56 (0.75); 9000 x 1024 x 1024
+    //   42 / 41 (0.56).
+    //   512 < K < 1536: 0.85.  16384 x 4096 x 1024 146 / 157 (1), 14,000 x 1024 x
+    //   1024 45.1 / 45.4 (0.86); 20,000 x 2048 x 1024 104 / 94 (0.82), 26,000 x
+    //   2048 x 1024 137 / 124 (0.80), 8192 x 3072 x 768 61 / 49 (0.75).
+    //   K = 512: only full waves.  65,536 x 512 x 512 89 / 102 (1), but 33,000 x
+    //   2048 x 512 124 / 102 (0.81), 57,000 x 1024 x 512 100 / 84 (0.87).
+    //   K < 512: none.  65,536 x 256 x 256 36 / 31 (1), 65,536 x 1024 x 256 83 / 72.
+    // Tiles of 128 from one per CU on: 15.3 us against 22.4 with 64 at 4095 x 2048
+    // x 512 (512 tiles); below that the smaller tiles spread the work further: 17.1
+    // against 28 at 4095 x 512 x 2048 (128 tiles), 41 against 46 at 3000 x 1024 x
+    // 4096 (192).
     auto tiles = [&](int t) { return g.N % t ? 0 : (int64_t)(g.N / t) * ((g.M + t - 1) / t); };
     const int64_t t256 = tiles(256), waves = (t256 + 255) / 256;
-    if (t256 > 0 && 4 * t256 >= 3 * 256 * waves) return launch_shape<GemmShape<256, 256, 64, 2>, IN, OUT>(g, stream);
+    const int fill = g.K >= 1536 ? 192 : (g.K > 512 ? 218 : (g.K == 512 ? 252 : 257));  // tiles per wave
+    if (t256 > 0 && t256 >= fill * waves) return launch_shape<GemmShape<256, 256, 64, 2>, IN, OUT>(g, stream);
     if (tiles(128) >= 256) return launch_shape<GemmShape<128, 128, 64, 2>, IN, OUT>(g, stream);
     return launch_shape<GemmShape<64, 64, 64, 4>, IN, OUT>(g, stream);
 }

@@ -13,9 +13,8 @@ from paper_2001_04451_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-# N = 128: only the smaller tiles; 64 x 64 tiles below 256 tiles of 128, 128 x 128
-# from there, 256 x 256 from 192 of them (M = 12033, N = 1024: 48 x 4, the last
-# row tile of one row).  K / 64 stages: 1, 2, 3, 5, 7.
+# N = 128: only the smaller tiles; 64 x 64 tiles below 256 tiles of 128, 128 x 128 from there (M = 12033, N = 1024:
+# 95 x 8, the last row tile of one row).  K / 64 stages: 1, 2, 3, 5, 7.
 @pytest.mark.parametrize("M,N,K", [(1, 128, 64), (63, 128, 128), (65, 384, 320), (300, 256, 448), (4097, 1024, 64),
                                    (5000, 896, 192), (12033, 1024, 64), (12033, 1024, 128), (12200, 1024, 448)])
 def test_linear_tiles(M, N, K):
@@ -36,6 +35,14 @@ def test_linear_tiles(M, N, K):
     assert ((relu.double() - exact.relu()).abs() <= bound + 2.0 ** -8 * exact.abs()).all()
 
 
+# 256 x 256 tiles on either side of where they begin (218 tiles from K = 576, 256 or 252 at K = 512, 192 from K = 1536;
+# the last row tile of one row): K / 64 = 8, 9, 11 and 24 stages.
+@pytest.mark.parametrize("M,N,K", [(16129, 1024, 512), (15873, 1024, 512), (15617, 1024, 512), (13825, 1024, 576),
+                                   (13569, 1024, 704), (7169, 2048, 704), (12033, 1024, 1536), (11777, 1024, 1536)])
+def test_linear_wide_tiles(M, N, K):
+    test_linear_tiles(M, N, K)
+
+
 # The walk over the tiles (bands of an eighth of the row tiles, four columns at a time, an eighth of the tiles to an XCD)
 # takes every tile once, whatever their counts: fewer than eight tiles, a short last band, a last group of one to three
 # columns.  Row and column counts in tiles of 64 (128 for the last two: 257 and 33 row tiles).
@@ -54,7 +61,7 @@ def test_linear_walk(M, N):
 
 
 # The attention half's products in the [B, H, L, 64] layout, batches ending inside row tiles.  The whole call takes
-# 256 x 256 tiles (M = 16362, N = 1024: 256 of them; M = 65000, N = 256: 254) or 128 x 128 (M = 33330, N = 128: 261),
+# 256 x 256 tiles (M = 16362, N = 1024: 256 of them) or 128 x 128 (M = 65000, N = 256: 1016; M = 33330, N = 128: 261),
 # a few batches 128 x 128 (M = 4848, N = 1024; M = 26000, N = 256) or 64 x 64 (M = 3333), one batch 64 x 64.  Every
 # tile adds a value's products in the same order, so the results are the same bits; one batch is held to the oracle.
 @pytest.mark.parametrize("B,H,L,few", [(54, 16, 303, 16), (50, 4, 1300, 20), (30, 2, 1111, 3)])
