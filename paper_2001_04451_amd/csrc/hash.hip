@@ -191,7 +191,7 @@ __device__ __forceinline__ float q_value(const void* q, int64_t row, int k) {
 // entries, in two passes:
 //  1. fp32 projections of every column on the matrix cores
 //     (v_mfma_f32_16x16x4_f32: 16 columns x 16 entries).  Wave w owns columns
-//     64 w .. 64 w + 63 as four tiles; k-step s of lane group g is t = 16 g + s,
+//     32 w .. 32 w + 31 as two tiles; k-step s of lane group g is t = 16 g + s,
 //     so a lane holds 16 consecutive values of its entry's q row and, per
 //     tile, 16 consecutive values of its column (r_t: R with its columns
 //     contiguous), loaded once per block, all in flight together.  The fp32
@@ -213,16 +213,20 @@ __device__ __forceinline__ float q_value(const void* q, int64_t row, int k) {
 // Measured against the earlier form (lane = entry, R by scalar loads one t
 // after another, 64 entries a block): 32 -> 6.2 us at L = 1K fp32, 23 -> 9.4
 // at 4 x 8 x 4K with 64 buckets, 39 -> 29 at 16 x 64K with 8 rounds of 1024.
+// Sixteen waves of two tiles hold R in registers without a spill (109 of 128);
+// eight of four tiles, two blocks to a CU, kept 36 to 100 bytes a lane in scratch.
+// Whole hash, us: 27.5 -> 25.0 at 4 x 8 x 4K with 64 buckets, 31.0 -> 28.6 at
+// 2 x 4 x 6001 fp32, 69.9 -> 66.3 at 2 x 8 x 16K, 72.4 -> 68.3 at 2 x 8 x 12K with
+// one R per head.
 // Long lists are dealt out over all blocks.  With each round's list left to its
-// own 512 / rounds blocks, one round of equal columns took the hash of 16 x 64K
-// (8 rounds) 64 ms against 16 now and 17 in the earlier form (256 blocks a
-// round), and a head of zero rows among 8 of 12K, one R each, 1.54 ms against
-// 0.4 and 1.29; ordinary calls the same in both (0.667 and 0.075 ms).
-constexpr int kRefineThreads = 512;
+// own blocks, one round of equal columns took the hash of 16 x 64K (8 rounds)
+// 63 ms against 16.6 now and 17 in the form of 256 blocks a round, and a head of
+// zero rows among 8 of 12K, one R each, 1.53 ms against 0.44 and 1.29.
+constexpr int kRefineThreads = 1024;
 constexpr int kRefineWaves = kRefineThreads / 64;
 constexpr int kRefineGroup = 16;     // entries per pass: a matrix tile's columns
 constexpr int kRefineCand = 8;       // candidate lanes per entry
-constexpr int kRefineTiles = 4;      // 16-column tiles per wave in pass 1
+constexpr int kRefineTiles = 2;      // 16-column tiles per wave in pass 1
 constexpr int kRefineOwn = 2;        // groups of its own round's list that a block takes before other rounds'
 static_assert(kRefineWaves * kRefineTiles * 16 >= 512, "pass 1 covers n_b / 2 <= 512 columns");
 
@@ -258,15 +262,16 @@ __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
     // after the block's own.
     const int rounds = gridDim.y, own = kRefineOwn * gridDim.x;
     for (int k0 = 0; k0 < rounds; k0 += 64) {
-    const int k_l = k0 + lane;
-    const int n_l = k_l < rounds ? counts[(blockIdx.y + k_l) % rounds] : 0;
+    const int k_l = k0 + lane, r_l = (int)blockIdx.y + k_l;
+    const int n_l = k_l < rounds ? counts[r_l < rounds ? r_l : r_l - rounds] : 0;
     uint64_t todo = __ballot((n_l + kRefineGroup - 1) / kRefineGroup >
                              (k_l == 0 ? 0 : own + k_l * (int)gridDim.x) + (int)blockIdx.x);
     for (; todo; todo &= todo - 1) {  // uniform per block
     const int kk = __ffsll((unsigned long long)todo) - 1;
     const int n = __builtin_amdgcn_readlane(n_l, kk);
     const int groups = (n + kRefineGroup - 1) / kRefineGroup;
-    const int r = (blockIdx.y + k0 + kk) % rounds;  // round of the R sets: r % n_r of its rows
+    int r = (int)blockIdx.y + k0 + kk;  // round of the R sets: r % n_r of its rows
+    r = r < rounds ? r : r - rounds;
     int32_t* buckets = buckets_ + r % n_r;
     const int* list = lists + list_stride * r;
     const float* Rt = r_t + (size_t)r * half_pad * kHeadDim;  // [column][t], zero columns up to half_pad
@@ -1287,10 +1292,10 @@ hipError_t launch_hash_sets(const void* q, bool f32, const Slices& sl, const Sli
     constexpr int kWaves = kHashWaves;
     const int64_t n_slices = sl.set_rows / sl.rows * sl.sets;
     const unsigned grid = (unsigned)(n_slices * sl.blocks);
-    // Refinement blocks: about two per CU over all rounds.  A typical list holds
-    // 0.1% of the rows (64 groups of 16 at 1M rows).
+    // Refinement blocks: one per CU over all rounds.  A typical list holds 0.1% of
+    // the rows (64 groups of 16 at 1M rows).
     const unsigned refine_blocks = (unsigned)std::max<int64_t>(
-        1, std::min<int64_t>(std::max(1, 512 / rounds), (sl.set_rows + kRefineGroup - 1) / kRefineGroup));
+        1, std::min<int64_t>(std::max(1, 256 / rounds), (sl.set_rows + kRefineGroup - 1) / kRefineGroup));
     if (f32) {
         launch_pass<true, kExact, kWaves>(
             PassArgs{q, sl, n_rounds, half, half_pad, w.r_hi, w.r_mid, cn_max, nullptr, acc_f32, nullptr, 0.f,
