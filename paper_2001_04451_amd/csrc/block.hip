@@ -21,9 +21,9 @@
 // bytes a cycle into a CU are as long as the products of a 128 x 128 tile.  A
 // 256 x 256 tile needs half of that; its single wave per SIMD then must not
 // issue anything in a row, so every copy and operand read stands alone between
-// two products.  16384 x 1024 x 4096 with residual: 185 -> 128 us (1.07
-// PFLOP/s), 16384 x 4096 x 1024 to bf16: 209 -> 167 us, 65536 x 1024 x 1024
-// with residual (0.67 GB): 321 -> 233 us; 4095 x 512 x 2048: 38 -> 17 us.
+// two products.  16384 x 1024 x 4096 with residual: 173 -> 119 us (1.15
+// PFLOP/s), 16384 x 4096 x 1024 to bf16: 183 -> 153 us, 65536 x 1024 x 1024
+// with residual (0.67 GB): 320 -> 215 us; 4095 x 512 x 2048: 38 -> 17 us.
 // Workgroups are numbered so that an XCD works on a block of row and column
 // tiles at a time and reads their rows of A and W from
 // memory once.  The epilogue adds the bias and either
@@ -145,7 +145,8 @@ struct GemmShape {
     // sixteen lanes, 0-3, 12-15, 20-23 and 24-27 the first of them (inferred
     // from SQ_LDS_BANK_CONFLICT under several layouts); under these slots a
     // group's rows and pieces meet all 64 banks once: no conflicts counted.
-    static __device__ __forceinline__ int slot(int row, int p) { return KB == 32 ? p ^ (-(row >> 2) & 3) : p ^ (row & 7); }
+    static_assert(KB == 64, "slots and head offsets of 64 k-values");
+    static __device__ __forceinline__ int slot(int row, int p) { return p ^ (row & 7); }
 };
 
 // Until at most N of the wave's loads are in flight and its LDS reads are
@@ -228,8 +229,7 @@ __global__ __launch_bounds__(256, (S::kLds > 80 * 1024 ? 1 : 2)) void gemm_bf16_
         const bool is_a = j < S::kLoadsA;
         uint32_t k_off;  // bytes along k: a head is 64 k-values
         if (IN == kInHeads && is_a)
-            k_off = S::KB == 64 ? (uint32_t)st * (uint32_t)g.L * 128u
-                                : (uint32_t)(st >> 1) * (uint32_t)g.L * 128u + (uint32_t)(st & 1) * 64u;
+            k_off = (uint32_t)st * (uint32_t)g.L * 128u;
         else
             k_off = (uint32_t)st * S::kRowBytes;
         const uint32_t run = is_a ? wave * S::kLoadsA + j : S::TM / S::kRunRows + wave * S::kLoadsW + (j - S::kLoadsA);

@@ -13,19 +13,22 @@
 //    a screened projection differs from the exact one by a bounded amount
 //    (residual, fp32 accumulation, and the index bits packed into the low
 //    mantissa).
-//  * R streams through LDS by direct global-to-LDS copies, 256 columns per
-//    stage, while each wave's products for the next tile are interleaved
-//    with the vector epilogue of the current one (one in-order instruction
-//    stream keeps both the matrix core and the vector ALUs busy).
+//  * R streams through LDS by direct global-to-LDS copies, up to 256 columns
+//    (128 in the screen, 64 with both planes of bf16 input) per stage, while
+//    each wave's products for the next tile are interleaved with the vector
+//    epilogue of the current one (one in-order instruction stream keeps both
+//    the matrix core and the vector ALUs busy).
 //  * Each lane keeps the two largest |projection| keys it has seen; the
 //    index inside a 32-column tile rides in the low bits of the key, so an
 //    and-or per projection and a max3, a med3 and a max per two suffice, and
 //    the tile of the best key is noted once per tile.  A row's ids for all
 //    rounds are written together at the end.
 //  * If the gap between the best and second-best key cannot rule out an
-//    exchange under the error bound, the row-round is appended to a list and
-//    recomputed afterwards over both planes, and what that leaves open in
-//    fp64 by a last kernel (same products and summation order as a plain
+//    exchange under the error bound, the row-round is appended to a list for
+//    the next pass.  Large bf16 calls are screened over the hi plane alone and
+//    their open row-rounds recomputed over both; small bf16 calls take both
+//    planes at once, fp32 calls both planes of q and R.  What these leave open a
+//    last kernel decides in fp64 (same products and summation order as a plain
 //    loop), so the ids always equal the exact argmax.
 #include "common.h"
 #include "launch.h"
@@ -450,10 +453,10 @@ __global__ __launch_bounds__(kRefineThreads, 4) void hash_refine_kernel(
 }
 
 // R streams through LDS in stages of ST tiles (32 ST columns) of one round,
-// NP planes, double-buffered: 2 x NP x 32 ST x 128 B, at most 128 KB (one
-// plane with ST = 16, two with ST = 8).  ST is the round's tile count
-// rounded up to a power of two, capped there, so small rounds compute no
-// idle tiles and large ones few barriers.  A stage is copied straight from
+// NP planes, double-buffered: 2 x NP x 32 ST x 128 B, at most 128 KB (two
+// planes with ST = 8; see launch_pass).  ST is the round's tile count rounded
+// up to a power of two, capped by the pass, so small rounds compute no idle
+// tiles and large ones few barriers.  A stage is copied straight from
 // global memory into LDS (buffer loads to LDS, no registers in between)
 // while the previous one is consumed, so there is one barrier per stage.  A
 // 16-byte piece p of column c sits at slot p ^ stage_swz(c) of the column's
@@ -1203,11 +1206,8 @@ void launch_pass(const PassArgs& a, dim3 grid, int rounds, hipStream_t stream) {
         launch_pass_st<F32, MODE, WAVES, 2>(a, grid, rounds, stream);
     else if (tpr <= 4 || kMax == 4) {
         if constexpr (kMax >= 4) launch_pass_st<F32, MODE, WAVES, 4>(a, grid, rounds, stream);
-    }
-    else if (tpr <= 8 || kMax == 8) {
-        if constexpr (kMax >= 8) launch_pass_st<F32, MODE, WAVES, 8>(a, grid, rounds, stream);
     } else {
-        if constexpr (kMax >= 16) launch_pass_st<F32, MODE, WAVES, 16>(a, grid, rounds, stream);
+        if constexpr (kMax >= 8) launch_pass_st<F32, MODE, WAVES, 8>(a, grid, rounds, stream);
     }
 }
 
@@ -1216,7 +1216,7 @@ void launch_pass(const PassArgs& a, dim3 grid, int rounds, hipStream_t stream) {
 namespace {
 
 // How a call's rows fall into slices and R sets.  With one R per head, the
-// heads are hashed together, up to kMaxRounds rounds of R at a time (which
+// heads are hashed together, up to kMaxSetRounds rounds of R at a time (which
 // bounds the planes' workspace at 256 MiB).
 constexpr int kMaxSetRounds = 1024;
 
@@ -1224,7 +1224,11 @@ constexpr int kMaxSetRounds = 1024;
 // both planes of R at once: twice the products, but no pass over the rows a
 // screen leaves open, which costs 10 us however few they are.  Whole hash,
 // one pass against screen and listed pass: 30.4 / 38.3 us at 8 M projections,
-// 39.2 / 43.3 at 32 M, 65.9 / 58.8 at 72 M, 78.7 / 70.2 at 128 M.
+// 39.2 / 43.3 at 32 M, 65.9 / 58.8 at 72 M, 78.7 / 70.2 at 128 M.  With one R
+// per head the line lies lower for few columns and higher for more: 16 heads of
+// 64 buckets 53 / 59 at 30 M and 72 / 67 at 39 M, 8 of 192 buckets 51 / 67 at
+// 42 M and 122 / 104 at 150 M; for 8 of 1024 buckets, few rows each, the screen is
+// the faster one at every size (129 / 111 at 10 M, 130 / 113 at 39 M).
 constexpr int64_t kSmallProjections = (int64_t)40 << 20;
 
 Slices slices_of(int64_t BH, int L, int heads, int n_rounds) {
