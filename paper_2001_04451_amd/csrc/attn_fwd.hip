@@ -471,11 +471,14 @@ __global__ __launch_bounds__((FwdGeom<M, AFTER>::kThreads), (FwdGeom<M, AFTER>::
 // of O^T += V^T P^T as they are.  k-step s of lane group g is dim 16 g + s of
 // S and key 4 g + s of P V.  Exponentials and logarithms are the library's
 // expf and logf in natural units; logits, weights and sums are fp32.
-// Bound by latency for small calls (two gathers and a barrier each) and by the
-// matrix cores for large ones (1024 cycles per tile of 16 x 16).  Against the
-// earlier kernel (a lane per query, every key row broadcast from LDS to 64
-// dependent FMAs): L = 1K, one head 44 -> 15 us; 2 x 4 x 6001, 4 rounds
-// 499 -> 108 us; errors against 64 bits unchanged (1e-7).
+// Bound by latency, in large calls too: at 2 x 4 x 6001 with 4 rounds (110 us)
+// the matrix cores are busy 17% of the time and the VALU 28%.  A workgroup has
+// 66 KB of LDS, two fit on a CU, and on average 1.4 waves a SIMD are there; each
+// piece costs the wait for its gather, two barriers and a pass over its rows for
+// the norms and the finiteness flag, and each row is gathered by the workgroups
+// of two chunks.  Against the earlier kernel (a lane per query, every key row
+// broadcast from LDS to 64 dependent FMAs): L = 1K, one head 44 -> 15 us;
+// 2 x 4 x 6001, 4 rounds 499 -> 110 us; errors against 64 bits unchanged (1e-7).
 constexpr int kPiece = 64;  // slots of a staged piece
 
 // LDS slots of the sixteen 16-byte pieces of an fp32 row.  K rows are read as
