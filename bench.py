@@ -47,7 +47,7 @@ CSRC = os.path.join(ROOT, "paper_2001_04451_amd", "csrc")
 # Stages as the library runs them: the kernels of each call, the source files
 # they are built from, and the peak that bounds the stage's main kernel.
 STAGES = {
-    "hash": {"kernels": ["prep_r_cols_kernel", "prep_r_max_kernel", "hash_kernel",
+    "hash": {"kernels": ["prep_r_kernel", "prep_r_max_kernel", "hash_kernel",
                          "hash_refine_kernel"],
              "sources": ["hash.hip", "common.h"], "bound": "mfma", "work": "hash_flop"},
     "sort": {"kernels": ["sort_hist_kernel", "sort_scan_kernel", "sort_scatter_kernel"],
